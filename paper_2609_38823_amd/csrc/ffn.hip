@@ -1296,6 +1296,370 @@ __global__ __launch_bounds__(PP_THR, 1) void ffn_pingpong_kernel(
   }
 }
 
+// ---------------------------------------------------------------------------
+// Persistent expert FFN for few rows per expert (decode).
+//
+// With a handful of rows per expert the call only streams weights, and what
+// bounds it is how many weight bytes the whole chip keeps in flight: one
+// token's eight experts are 48 gate/up items of 128 columns, each a 1 MB
+// stream of one workgroup, and leave most compute units idle.  Here an item
+// is one 32-row weight block pair (gate/up: 32 gate rows and their 32 up
+// rows; down: 64 rows), and its four wavefronts split the reduction: wave w
+// takes the w-th quarter of the k-values, and the four partial tiles are
+// added in LDS in wave order.  Eight 16-wide k-blocks (2 KB of weights each;
+// four where the tile has more than 32 rows) are in flight per wavefront.  The token
+// rows are read straight into the MFMA operand (rows past the tile's end
+// lie outside the buffer and move nothing).
+//
+// Items are dealt over eight queues one by one (no per-XCD split of whole
+// tiles: a few live experts do not divide evenly over eight XCDs), so a down
+// item's h rows may come from other XCDs: h is stored and loaded with
+// agent scope (sc1: written through, and read past, the XCD's own L2).  A
+// down item issues its first weights before it waits for its tile's gate/up
+// items, which were all claimed before it by running workgroups.
+// ---------------------------------------------------------------------------
+constexpr int SK_BM = 64;              // token rows per tile (one or two 32-row blocks)
+constexpr int AUX_NT = 2, AUX_SC1 = 16;  // non-temporal; agent scope
+
+constexpr int SK_LDS = 4 * 2 * (SK_BM / 32) * 4 * 64 * 16;  // partial tiles of the four wavefronts
+
+// One item with MA 32-row token blocks.  `claim`: when not null, thread 0
+// claims the workgroup's next item once the last weights are issued, and
+// leaves it in *s_next (published by the barrier below).
+template <int MODE, int MA, bool ROWMAJOR>
+__device__ __forceinline__ void skinny_tile(const uint16_t* __restrict__ A, const uint16_t* __restrict__ Wp,
+                                            uint16_t* __restrict__ C, const Work wk, int d, int m,
+                                            const RowGather gather, char* lds, const int* done, int nn0,
+                                            int* gave_up, int* claim, int* s_next) {
+  constexpr int RING = MA == 1 ? 8 : 4;  // k-blocks in flight (the registers' limit)
+  const int nt = wk.nt;
+  const int Kdim = MODE == 0 ? d : m;
+  const int R = MODE == 0 ? 2 * m : d;
+  const int ldc = MODE == 0 ? m : d;
+  const int RB = R / 32;
+  const int nkb = Kdim / 64;  // k-blocks per wavefront: a multiple of 4 (row-major weights: of 2)
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));  // keep the per-item offsets out of the item loop
+  const int lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r32 = lane & 31, kh = lane >> 5;
+
+  // token rows: an offset past every buffer for rows the tile does not have
+  const bool gat = MODE == 0 && gather.src_of_row != nullptr;
+  const __amdgpu_buffer_rsrc_t a_rs =
+      gat ? make_rsrc(A, (uint32_t)gather.T * Kdim * 2)
+          : make_rsrc(A + (size_t)wk.row0 * Kdim, (uint32_t)wk.rows * Kdim * 2);
+  int src[MA];
+#pragma unroll
+  for (int mi = 0; mi < MA; ++mi) {
+    const int row = mi * 32 + r32;
+    src[mi] = row;
+    if (gat) src[mi] = gather.src_of_row[wk.row0 + (row < wk.rows ? row : 0)];
+  }
+
+  const __amdgpu_buffer_rsrc_t b_rs = make_rsrc(Wp + (size_t)wk.expert * R * Kdim, (uint32_t)R * Kdim * 2);
+  const int rb0 = MODE == 0 ? nt : 2 * nt;
+  const int rb1 = MODE == 0 ? m / 32 + nt : rb0 + 1;
+  const int kb0 = wv * nkb;
+  // row-major weights: lane l reads the same 16 bytes from their place in
+  // row 32 rb + l % 32
+  const int b_voff = ROWMAJOR ? (r32 * Kdim + 8 * kh) * 2 : lane * 16;
+  u32x4 bq[RING][2], aq[RING][MA];
+  auto load_b = [&](u32x4 (&b)[2], int kb) {
+    if constexpr (ROWMAJOR) {
+      b[0] = load_frag<0>(b_rs, b_voff, rb0 * 64 * Kdim + (kb0 + kb) * 32);
+      b[1] = load_frag<0>(b_rs, b_voff, rb1 * 64 * Kdim + (kb0 + kb) * 32);
+    } else {
+      b[0] = load_frag<AUX_NT>(b_rs, b_voff, ((kb0 + kb) * RB + rb0) * 1024);
+      b[1] = load_frag<AUX_NT>(b_rs, b_voff, ((kb0 + kb) * RB + rb1) * 1024);
+    }
+  };
+  int a_voff[MA];
+  auto load_a = [&](u32x4 (&a)[MA], int kb) {
+#pragma unroll
+    for (int mi = 0; mi < MA; ++mi) a[mi] = load_frag<MODE == 1 ? AUX_SC1 : 0>(a_rs, a_voff[mi], (kb0 + kb) * 32);
+  };
+
+  f32x16 acc[2][MA];
+#pragma unroll
+  for (int f = 0; f < 2; ++f)
+#pragma unroll
+    for (int mi = 0; mi < MA; ++mi)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[f][mi][e] = 0.f;
+  auto mma = [&](const u32x4 (&b)[2], const u32x4 (&a)[MA]) {
+#pragma unroll
+    for (int mi = 0; mi < MA; ++mi)
+#pragma unroll
+      for (int f = 0; f < 2; ++f)
+        acc[f][mi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, b[f]),
+                                                             __builtin_bit_cast(bf16x8, a[mi]), acc[f][mi], 0, 0, 0);
+  };
+  auto rows_ready = [&]() {
+    if (MODE == 1 && done) wait_gate_up(done, nn0, gave_up);
+#pragma unroll
+    for (int mi = 0; mi < MA; ++mi) {
+      const int row = mi * 32 + r32;
+      int t = src[mi];
+      if (gat) {
+        t /= gather.k;
+        if ((unsigned)t >= (unsigned)gather.T) t = 0;
+      }
+      a_voff[mi] = row < wk.rows ? (t * Kdim + 8 * kh) * 2 : (int)0xf0000000u;
+    }
+  };
+  int next = 0;
+  auto claim_next = [&]() {
+    int* c = claim;
+    asm volatile("" : "+v"(c));  // a per-lane address: the result is not broadcast (and waited for) here
+    if (claim && tid == 0) next = atomicAdd(c, 1);
+  };
+
+  // k-block i sits in slot i % RING.  Packed weights: a slot is refilled with
+  // k-block i + RING as soon as its MFMAs are issued.  Row-major weights:
+  // four slots at a time, so that the four loads that share each 128-byte
+  // line leave together.  N k-blocks of the last RING + N are refills.
+  constexpr int GRP = ROWMAJOR ? 4 : 1;
+  int i = 0;
+  auto refill = [&](int u0) {
+#pragma unroll
+    for (int u = u0; u < u0 + GRP; ++u) mma(bq[u % RING], aq[u % RING]);
+#pragma unroll
+    for (int u = u0; u < u0 + GRP; ++u) {
+      load_b(bq[u % RING], i + RING + u);
+      load_a(aq[u % RING], i + RING + u);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto finish = [&](auto N) {
+    constexpr int n = decltype(N)::value;
+#pragma unroll
+    for (int u = 0; u + GRP <= n; u += GRP) refill(u);
+    if constexpr (n % GRP != 0) {
+#pragma unroll
+      for (int u = n - n % GRP; u < n; ++u) {
+        mma(bq[u % RING], aq[u % RING]);
+        load_b(bq[u % RING], i + RING + u);
+        load_a(aq[u % RING], i + RING + u);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    claim_next();
+#pragma unroll
+    for (int u = n; u < n + RING; ++u) mma(bq[u % RING], aq[u % RING]);
+  };
+  auto whole = [&](auto N) {  // fewer k-blocks than the ring holds
+    constexpr int n = decltype(N)::value;
+#pragma unroll
+    for (int u = 0; u < n; ++u) load_b(bq[u], u);
+    rows_ready();
+#pragma unroll
+    for (int u = 0; u < n; ++u) load_a(aq[u], u);
+    claim_next();
+#pragma unroll
+    for (int u = 0; u < n; ++u) mma(bq[u], aq[u]);
+  };
+  using N0 = std::integral_constant<int, 0>;
+  using N2 = std::integral_constant<int, 2>;
+  using N4 = std::integral_constant<int, 4>;
+  using N6 = std::integral_constant<int, 6>;
+  if (nkb < RING) {
+    if constexpr (ROWMAJOR) {
+      if (nkb == 2) whole(N2{});
+      if (RING > 4 && nkb == 6) whole(N6{});
+    }
+    if (RING > 4 && nkb == 4) whole(N4{});
+  } else {
+#pragma unroll
+    for (int u = 0; u < RING; ++u) load_b(bq[u], u);
+    __builtin_amdgcn_sched_barrier(0);
+    rows_ready();
+#pragma unroll
+    for (int u = 0; u < RING; ++u) load_a(aq[u], u);
+    __builtin_amdgcn_sched_barrier(0);
+    for (; i + 2 * RING <= nkb; i += RING) {
+#pragma unroll
+      for (int u = 0; u < RING; u += GRP) refill(u);
+    }
+    const int n = nkb - i - RING;
+    if (n == 0) finish(N0{});
+    if constexpr (RING > 4)
+      if (n == 4) finish(N4{});
+    if constexpr (ROWMAJOR) {
+      if (n == 2) finish(N2{});
+      if constexpr (RING > 4)
+        if (n == 6) finish(N6{});
+    }
+  }
+
+  // partial tiles to LDS: element group g (columns 8 g + 4 (lane / 32) .. + 3
+  // of the 32-row weight block) of lane l at [wave][block f][mi][g][lane]
+  f32x4* part = reinterpret_cast<f32x4*>(lds);
+#pragma unroll
+  for (int f = 0; f < 2; ++f)
+#pragma unroll
+    for (int mi = 0; mi < MA; ++mi)
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        part[(((wv * 2 + f) * MA + mi) * 4 + g) * 64 + lane] =
+            f32x4{acc[f][mi][4 * g], acc[f][mi][4 * g + 1], acc[f][mi][4 * g + 2], acc[f][mi][4 * g + 3]};
+  if (claim && tid == 0) *s_next = next;
+  __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_sched_barrier(0);
+  // wave w adds element group w of both blocks, in wave order
+  const __amdgpu_buffer_rsrc_t c_rs =
+      make_rsrc(C + (size_t)wk.row0 * ldc, (uint32_t)wk.rows * (uint32_t)ldc * 2);
+#pragma unroll
+  for (int mi = 0; mi < MA; ++mi) {
+    f32x4 v[2];
+#pragma unroll
+    for (int f = 0; f < 2; ++f) {
+      v[f] = part[((f * MA + mi) * 4 + wv) * 64 + lane];
+#pragma unroll
+      for (int w = 1; w < 4; ++w) v[f] += part[(((w * 2 + f) * MA + mi) * 4 + wv) * 64 + lane];
+    }
+    typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+    const int off = ((mi * 32 + r32) * ldc + 8 * wv + 4 * kh) * 2;  // rows past the tile: outside the buffer
+    if (MODE == 0) {
+      const u32x2 pk = {pack_bf16x2(swiglu_f(v[0][0], v[1][0]), swiglu_f(v[0][1], v[1][1])),
+                        pack_bf16x2(swiglu_f(v[0][2], v[1][2]), swiglu_f(v[0][3], v[1][3]))};
+      __builtin_amdgcn_raw_buffer_store_b64(pk, c_rs, off, nt * 64, AUX_SC1);
+    } else {
+#pragma unroll
+      for (int f = 0; f < 2; ++f) {
+        const u32x2 pk = {pack_bf16x2(v[f][0], v[f][1]), pack_bf16x2(v[f][2], v[f][3])};
+        __builtin_amdgcn_raw_buffer_store_b64(pk, c_rs, off + f * 64, nt * 128, 0);
+      }
+    }
+  }
+}
+
+template <int MODE, bool ROWMAJOR = false>
+__device__ __forceinline__ void skinny_item(const uint16_t* __restrict__ A, const uint16_t* __restrict__ Wp,
+                                            uint16_t* __restrict__ C, const Work wk, int d, int m,
+                                            const RowGather gather, char* lds, const int* done, int nn0,
+                                            int* gave_up, int* claim, int* s_next) {
+  if (wk.rows > 32)
+    skinny_tile<MODE, 2, ROWMAJOR>(A, Wp, C, wk, d, m, gather, lds, done, nn0, gave_up, claim, s_next);
+  else
+    skinny_tile<MODE, 1, ROWMAJOR>(A, Wp, C, wk, d, m, gather, lds, done, nn0, gave_up, claim, s_next);
+}
+
+// one launch per GEMM on the same items: row-major weights, and packed ones
+// where the persistent kernel is not used (the same order of additions)
+template <int MODE, bool ROWMAJOR>
+__global__ __launch_bounds__(NTHR, 2) void ffn_gemm_skinny_kernel(
+    const uint16_t* __restrict__ A, const uint16_t* __restrict__ W, uint16_t* __restrict__ C, const Tiles tl,
+    int d, int m, const RowGather gather, const Guard g) {
+  if (guard_skip(g)) return;
+  __shared__ __attribute__((aligned(1024))) char lds[SK_LDS];
+  Work wk;
+  if (!find_work(tl, true, wk, lds)) return;
+  skinny_item<MODE, ROWMAJOR>(A, W, C, wk, d, m, gather, lds, nullptr, 0, nullptr, nullptr, nullptr);
+}
+
+// The queues: item j of a phase (gate/up, then down) is entry j / 8 of queue
+// j % 8, whose counters sit in header block j % 8 (gate/up claims at +0, down
+// claims at +4; 64 bytes from the next block's).  One counter for all would
+// be the bound: atomics of the whole chip on one address are served one
+// after another (64 tokens with one queue: 166 us, with eight 146).
+// A workgroup serves queue blockIdx % 8 and, when that is empty, any queue of
+// the same phase that is not; it goes on to the down items only when every
+// gate/up queue is empty, so every gate/up item is then claimed by a running
+// workgroup and a down item's wait ends.
+constexpr int SK_Q = 8;
+struct SkClaim {
+  int phase, q, i;  // entry i of queue q (i raw: may lie past the queue's end)
+};
+// Resolves a claim to an item number, or to n_all when nothing is left.  All
+// threads of wavefront 0 call it together.
+__device__ __forceinline__ int sk_resolve(SkClaim& c, int* ctr, int n_gu, int n_dn) {
+  for (;;) {
+    const int n = c.phase ? n_dn : n_gu;
+    if (c.i < (n - c.q + SK_Q - 1) / SK_Q) return (c.phase ? n_gu : 0) + c.i * SK_Q + c.q;
+    // this queue is empty: one look at all of them
+    const int l = threadIdx.x & (SK_Q - 1);
+    const int seen = __hip_atomic_load(ctr + 16 * l + 4 * c.phase, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const unsigned left = (unsigned)__ballot(threadIdx.x < SK_Q && seen < (n - l + SK_Q - 1) / SK_Q);
+    if (left) {  // the next one after q that has entries
+      const unsigned rot = (left >> (c.q + 1)) << (c.q + 1);
+      c.q = __ffs(rot ? rot : left) - 1;
+    } else {
+      if (c.phase) return n_gu + n_dn;
+      c.phase = 1;
+      c.q = blockIdx.x & (SK_Q - 1);
+    }
+    int got = 0;
+    if (threadIdx.x == 0) got = atomicAdd(ctr + 16 * c.q + 4 * c.phase, 1);
+    c.i = __builtin_amdgcn_readfirstlane(got);
+  }
+}
+
+__global__ __launch_bounds__(NTHR, 2) void ffn_skinny_kernel(
+    const uint16_t* __restrict__ X, const uint16_t* __restrict__ Wgu, const uint16_t* __restrict__ Wdn,
+    uint16_t* __restrict__ H, uint16_t* __restrict__ Y, const Tiles tl, int nn1, int d, int m,
+    const RowGather gather, int* __restrict__ ctr, const Guard g) {
+  if (guard_skip(g)) return;
+  __shared__ __attribute__((aligned(1024))) char lds[SK_LDS];
+  __shared__ int s_tstart[FFN_MAXE + 1];
+  __shared__ int s_off[FFN_MAXE + 1];
+  __shared__ int s_part[2 * (NTHR / 64) + 3];
+  __shared__ int s_next, s_item;
+  const int tid = threadIdx.x;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  SkClaim cl{0, (int)(blockIdx.x & (SK_Q - 1)), 0};
+  if (tid == 0) s_next = atomicAdd(ctr + 16 * cl.q, 1);  // published by the plan's barriers
+  for (int e = tid; e <= tl.E; e += NTHR) s_off[e] = clampi(tl.offsets[e], 0, tl.rows_max);
+  const XcdRange rg = plan_tiles<NTHR>(tl, 0, 1, s_tstart, s_part);
+  const int n_gu = rg.a1 * tl.nn, n_dn = rg.a1 * nn1;
+  if (blockIdx.x == 0 && tid == 0) ctr[3] = n_gu + n_dn;
+  int n_done = 0;
+  for (;; ++n_done) {
+    if (wv == 0) {
+      cl.i = __builtin_amdgcn_readfirstlane(s_next);
+      const int j = sk_resolve(cl, ctr, n_gu, n_dn);
+      if (tid == 0) s_item = j;
+    }
+    __syncthreads();
+    const int j = __builtin_amdgcn_readfirstlane(s_item);
+    if (j >= n_gu + n_dn) break;
+    // gate/up items first; expert-major, then n-tile, then m-tile
+    const bool down = j >= n_gu;
+    const int nn = down ? nn1 : tl.nn;
+    const int jm = down ? j - n_gu : j;
+    const int tq = jm / nn;
+    int a = 0, b = tl.E;  // tstart[a] <= tq < tstart[b]
+    while (b - a > 1) {
+      const int mid = (a + b) >> 1;
+      if (s_tstart[mid] <= tq) a = mid; else b = mid;
+    }
+    const int t_lo = s_tstart[a], c = s_tstart[a + 1] - t_lo;
+    const int o = jm - nn * t_lo;
+    const int t = t_lo + o % c;
+    const int r0 = s_off[a] + (t - t_lo) * SK_BM;
+    Work wk;
+    wk.expert = __builtin_amdgcn_readfirstlane(a);
+    wk.row0 = __builtin_amdgcn_readfirstlane(r0);
+    wk.rows = __builtin_amdgcn_readfirstlane(min(SK_BM, max(s_off[a + 1], s_off[a]) - r0));
+    wk.nt = __builtin_amdgcn_readfirstlane(o / c);
+    int* const done = ctr + FFN_CTR_TILES + __builtin_amdgcn_readfirstlane(t);
+    // the next claim, from the same queue (wavefront 0 knows it)
+    int* const claim = ctr + 16 * cl.q + 4 * cl.phase;
+    if (!down)
+      skinny_item<0>(X, Wgu, H, wk, d, m, gather, lds, nullptr, 0, nullptr, claim, &s_next);
+    else
+      skinny_item<1>(H, Wdn, Y, wk, d, m, RowGather{nullptr, 1, 0}, lds, done, tl.nn, ctr + 2, claim, &s_next);
+    // the h stores of every wavefront are complete (vmcnt 0) before the item
+    // is counted; the barrier also frees the LDS tiles
+    if (!down) __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (!down && tid == 0) __hip_atomic_fetch_add(done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  if (tid == 0 && n_done)
+    __hip_atomic_fetch_add(ctr + 16 * (blockIdx.x & 7) + 1, n_done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 __device__ __forceinline__ float silu_f(float g) { return g / (1.f + expf(-g)); }
 
 // ---------------------------------------------------------------------------
@@ -1371,6 +1735,8 @@ using kern::clear_kernel;
 using kern::ffn_status_kernel;
 using kern::ffn_fused_kernel;
 using kern::ffn_pingpong_kernel;
+using kern::ffn_skinny_kernel;
+using kern::ffn_gemm_skinny_kernel;
 using kern::ffn_gemm_packed_kernel;
 using kern::pack_weights_kernel;
 
@@ -1404,6 +1770,14 @@ void n_tiles_of(bool bf16, bool packed, int d, int m, int& nn0, int& nn1, bool& 
   }
 }
 
+// Whether the call runs the few-rows items (ffn_skinny_kernel): up to half a
+// row per expert on average, where the wide tiles leave most of the chip idle
+// (Qwen3-VL layer, top-8, clearing launch included: 1 token 61 -> 31 us, 2
+// tokens 65 -> 42, 4 tokens 73 -> 63, 8 tokens 87 -> 84; 23 tokens 108 -> 117,
+// where the wide tiles already stream at the memory's rate).  Row-major
+// weights follow the same rule, so that both layouts add in the same order.
+bool use_skinny(int bm, int rows_max, int E) { return bm == kern::SK_BM && 2 * rows_max <= E; }
+
 // kernels are instantiated here, outside any function template (device stubs
 // of kernels first instantiated inside a template launcher are not emitted)
 #define FFN_GEMM(MODE, BM, BN)                                                   \
@@ -1412,6 +1786,17 @@ void n_tiles_of(bool bf16, bool packed, int d, int m, int& nn0, int& nn1, bool& 
 // row-major bf16 weights: one launch per GEMM
 hipError_t launch_gemm(int mode, int bm, bool wide, const Tiles& tl, const uint16_t* A,
                        const uint16_t* W, uint16_t* C, int d, int m, hipStream_t s, Guard g) {
+  if (use_skinny(bm, tl.rows_max, tl.E)) {
+    Tiles ts = tl;
+    ts.nn = mode == 0 ? m / 32 : d / 64;
+    const int grid = (ts.max_tiles * ts.nn + 7) & ~7;
+    const RowGather none{nullptr, 1, 0};
+    if (mode == 0)
+      ffn_gemm_skinny_kernel<0, true><<<grid, NTHR, 0, s>>>(A, W, C, ts, d, m, none, g);
+    else
+      ffn_gemm_skinny_kernel<1, true><<<grid, NTHR, 0, s>>>(A, W, C, ts, d, m, none, g);
+    return hipGetLastError();
+  }
   const int grid = (tl.max_tiles * tl.nn + 7) & ~7;  // whole XCD rounds
   if (mode == 0) {
     if (bm == 128) {
@@ -1467,6 +1852,7 @@ hipError_t launch_packed(int bm, const Tiles& t0, int nn1, const uint16_t* X, co
                          const uint16_t* Wdn, uint16_t* H, uint16_t* Y, int d, int m,
                          const RowGather g0, int* ctr, hipStream_t s, Guard g, bool counters_ready) {
   int grid = 0, n_xcc = 0;
+  const bool skinny = use_skinny(bm, t0.rows_max, t0.E);
   if (persistent_shape(grid, n_xcc)) {
     if (!counters_ready) {
       hipError_t e = clear_counters(ctr, t0.max_tiles, FFN_PATH_PERSISTENT, s, g);
@@ -1476,6 +1862,19 @@ hipError_t launch_packed(int bm, const Tiles& t0, int nn1, const uint16_t* X, co
     // weight tile is read once and streams with the non-temporal hint
     // (measured at 64 tokens x top-8 over 93 experts: 166 -> 151 us)
     const bool stream_weights = bm == 64 && t0.rows_max <= 16 * t0.E;
+    if (skinny) {
+      Tiles ts = t0;
+      ts.nn = m / 32;
+      const int nn1s = d / 64;
+      // one workgroup per compute unit (two are slower: 2 tokens 42 -> 64 us,
+      // 8 tokens 84 -> 89), fewer when the items of at most one tile per row
+      // cannot occupy them
+      const int tiles = t0.max_tiles < t0.rows_max ? t0.max_tiles : t0.rows_max;
+      const int most = tiles * (ts.nn > nn1s ? ts.nn : nn1s);
+      ffn_skinny_kernel<<<grid / 2 < most ? grid / 2 : most, NTHR, 0, s>>>(X, Wgu, Wdn, H, Y, ts, nn1s, d, m, g0,
+                                                                          ctr, g);
+      return hipGetLastError();
+    }
     // 64-row tiles (few rows per expert, weight streaming): 128-row weight
     // tiles in the down GEMM, twice as many items of half the bytes, so that
     // the queues drain evenly at the end (64 tokens x top-8 through 48
@@ -1503,7 +1902,14 @@ hipError_t launch_packed(int bm, const Tiles& t0, int nn1, const uint16_t* X, co
     const uint16_t* W = Wgu;
     uint16_t* C = H;
     const RowGather rg = g0;
-    if (bm == 128) FFN_PACKED(0, 128); else FFN_PACKED(0, 64);
+    if (skinny) {
+      Tiles ts = t0;
+      ts.nn = m / 32;
+      ffn_gemm_skinny_kernel<0, false><<<(ts.max_tiles * ts.nn + 7) & ~7, NTHR, 0, s>>>(A, W, C, ts, d, m, rg, g);
+    } else if (bm == 128)
+      FFN_PACKED(0, 128);
+    else
+      FFN_PACKED(0, 64);
   }
   e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -1514,7 +1920,13 @@ hipError_t launch_packed(int bm, const Tiles& t0, int nn1, const uint16_t* X, co
     const uint16_t* W = Wdn;
     uint16_t* C = Y;
     const RowGather rg{nullptr, 1, 0};
-    if (bm == 128) FFN_PACKED(1, 128); else FFN_PACKED(1, 64);
+    if (skinny) {
+      t.nn = d / 64;
+      ffn_gemm_skinny_kernel<1, false><<<(t.max_tiles * t.nn + 7) & ~7, NTHR, 0, s>>>(A, W, C, t, d, m, rg, g);
+    } else if (bm == 128)
+      FFN_PACKED(1, 128);
+    else
+      FFN_PACKED(1, 64);
   }
   return hipGetLastError();
 }

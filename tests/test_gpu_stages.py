@@ -1219,6 +1219,52 @@ def test_persistent_ffn_repeated_calls_bitwise(T, monkeypatch):
     assert (s_h[:, 1] == s_h[:, 2]).all() and (s_h[:, 2] == s_h[0, 2]).all() and s_h[0, 2] > 0
 
 
+# at most half a row per expert on average: items of one 32-row weight block
+# pair with the k-values split over the wavefronts.  Rows per tile around 32
+# and 64, one to three tiles of an expert, and every remainder of the k loop
+# (k-blocks per wavefront: 4, 8, 12, 16, 24, 32; row-major weights: also 2,
+# 6, 10, 14)
+@pytest.mark.parametrize("E,d,m,cnt,packed", [
+    (16, 2048, 768, [1, 0, 0, 2, 0, 0, 0, 0, 5], True),
+    (300, 256, 256, [0, 31, 32, 33, 0, 1], True),
+    (500, 512, 768, [64, 65, 63, 0, 2], True),
+    (400, 1024, 512, [0, 130, 0, 40], True),
+    (24, 1536, 256, [0, 0, 11, 1], True),
+    (128, 256, 640, [0, 33, 1, 30], False),
+    (150, 768, 384, [3, 0, 66, 1], False),
+    (40, 256, 128, [0, 20], False),
+    (40, 512, 896, [0, 7, 13], False),
+])
+def test_few_rows_ffn(E, d, m, cnt, packed, monkeypatch):
+    counts = np.zeros(E, np.int64)
+    counts[:len(cnt)] = cnt
+    rows = int(counts.sum())
+    assert 2 * rows <= E
+    sh = I.LayerShape(d=d, E=E, m=m, k=1, dtype="bf16")
+    prm = I.layer_params(sh, seed=E + m)
+    offsets = dev(np.concatenate([[0], np.cumsum(counts)]).astype(np.int32))
+    xp = dev(I.synthetic_rows(rows, d, "bf16", seed=rows), torch.bfloat16)
+    wgu, wd = dev(prm["w_gate_up"], torch.bfloat16), dev(prm["w_down"], torch.bfloat16)
+    ws = torch.empty(abi.moe_workspace_size(rows, E, 1, d, m, 1), dtype=torch.uint8, device="cuda")
+    y = torch.full((rows, d), 7.0, dtype=torch.bfloat16, device="cuda")
+    abi.moe_expert_ffn(xp, offsets, wgu, wd, y, ws)
+    ref = oracle.expert_ffn_rows(host(xp), np.repeat(np.arange(E), counts), prm["w_gate_up"], prm["w_down"])
+    assert rel_inf(host(y), ref) <= TOL["bf16"]
+    assert row_rel(host(y), ref) <= TOL["bf16"]
+    if not packed:
+        return
+    wgu_p, wd_p = torch.empty_like(wgu), torch.empty_like(wd)
+    abi.moe_pack_expert_weights(wgu, wgu_p)
+    abi.moe_pack_expert_weights(wd, wd_p)
+    for two in ("0", "1", "0"):  # persistent, one launch per GEMM, persistent: the same bits
+        monkeypatch.setenv("DECOMOE_FFN_TWO_LAUNCH", two)
+        yp = torch.full((rows, d), 7.0, dtype=torch.bfloat16, device="cuda")
+        abi.moe_expert_ffn_packed(xp, offsets, wgu_p, wd_p, yp, ws)
+        path, _ = assert_ffn_ran_all(ws)
+        assert path == (abi.FFN_PATH_TWO_LAUNCH if two == "1" else abi.FFN_PATH_PERSISTENT)
+        assert torch.equal(yp.view(torch.int16), y.view(torch.int16))
+
+
 def test_expert_ffn_packed_gather_out_of_range_rows_read_token_zero():
     T, E, k, d, m = 64, 4, 2, 512, 256
     sh = I.LayerShape(d=d, E=E, m=m, k=k, dtype="bf16")
