@@ -23,7 +23,7 @@
 //                      with per-XCD work queues (the down GEMM of a token
 //                      tile starts as soon as its h is complete), or one
 //                      launch per GEMM where the XCD count is unknown
-// float32: a plain LDS-tiled SIMT kernel (correctness path for small layers).
+// float32: float32 MFMA, the k-values split over the wavefronts (small layers).
 #include <cstdlib>
 #include <type_traits>
 
@@ -1663,69 +1663,133 @@ __global__ __launch_bounds__(NTHR, 2) void ffn_skinny_kernel(
 __device__ __forceinline__ float silu_f(float g) { return g / (1.f + expf(-g)); }
 
 // ---------------------------------------------------------------------------
-// float32 SIMT path: 32x32 output tiles, k-step 32, 256 threads x 2x2 outputs
+// float32 path on float32 MFMA (v_mfma_f32_16x16x4f32): 32 token rows x 64
+// weight rows per workgroup (gate/up: 32 gate rows and their 32 up rows).
+// The layers it serves are small (a few rows per expert, k of a few hundred),
+// so the call is bound by latency, not by rate: the four wavefronts split the
+// k-values (32-wide chunks in turn) and load both operands straight into
+// registers, one chunk ahead, and the four partial tiles are added in LDS in
+// wave order.  Within a chunk lane l (row l % 16, q = l / 16) holds the eight
+// values 8 q .. 8 q + 7 of its row on both sides and MFMA step s consumes
+// k = 8 q + s, so every load is 16 bytes (VEC: rows of whole 16-byte
+// vectors; else element by element).  Values past the row's end are zero.
+// (512 tokens, d 256, 16 experts of m 128, top-2: 11 + 7 us; an LDS-tiled
+// kernel of 2 x 2 outputs per thread took 35 + 16.)
 // ---------------------------------------------------------------------------
-constexpr int FBM = 32, FBN = 32, FBK = 32;
+constexpr int FBM = 32, FBN0 = 32, FBN1 = 64, FBK = 32;
 
-template <int MODE>
+template <int MODE, bool VEC>
 __global__ __launch_bounds__(256) void ffn_gemm_f32_kernel(const float* __restrict__ A,
                                                            const float* __restrict__ W,
                                                            float* __restrict__ C,
                                                            const Tiles tl, int d, int m, const Guard g) {
   if (guard_skip(g)) return;
-  __shared__ float as[FBM][FBK + 1];
-  __shared__ float bs[2][FBN][FBK + 1];  // MODE 0: gate, up; MODE 1: down only
+  __shared__ f32x4 part[4][8][64];  // [wave][row block i, column block b][lane]
   __shared__ __attribute__((aligned(16))) char wl[64];
   Work wk;
   if (!find_work(tl, false, wk, wl)) return;
-  const int nt = wk.nt;
-  struct { int row0, rows, expert; } tile{wk.row0, wk.rows, wk.expert};
   const int Kdim = MODE == 0 ? d : m;
   const int Ncols = MODE == 0 ? m : d;
-  const float* Wexp = W + (size_t)tile.expert * (size_t)(MODE == 0 ? 2 * m : d) * Kdim;
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  float acc[2][2][2] = {};  // [B part][row][col]
-  for (int k0 = 0; k0 < Kdim; k0 += FBK) {
-    for (int i = tid; i < FBM * FBK; i += 256) {
-      int r = i / FBK, kk = i % FBK;
-      int kg = k0 + kk;
-      as[r][kk] = (r < tile.rows && kg < Kdim) ? A[(size_t)(tile.row0 + r) * Kdim + kg] : 0.f;
-      int col = nt * FBN + r;
-      bool ok = col < Ncols && kg < Kdim;
-      bs[0][r][kk] = ok ? Wexp[(size_t)col * Kdim + kg] : 0.f;
-      if (MODE == 0) bs[1][r][kk] = ok ? Wexp[(size_t)(m + col) * Kdim + kg] : 0.f;
-    }
-    __syncthreads();
-    for (int kk = 0; kk < FBK; ++kk) {
+  const int n0 = wk.nt * (MODE == 0 ? FBN0 : FBN1);
+  const float* Wexp = W + (size_t)wk.expert * (size_t)(MODE == 0 ? 2 * m : d) * Kdim;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r16 = lane & 15, q = lane >> 4;
+  // rows and columns past the tile's re-read its last ones (not stored)
+  const float* ap[2];
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        float a = as[ty * 2 + i][kk];
+  for (int i = 0; i < 2; ++i) ap[i] = A + (size_t)(wk.row0 + min(16 * i + r16, wk.rows - 1)) * Kdim;
+  const float* bp[4];
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          acc[0][i][j] = fmaf(a, bs[0][tx * 2 + j][kk], acc[0][i][j]);
-          if (MODE == 0) acc[1][i][j] = fmaf(a, bs[1][tx * 2 + j][kk], acc[1][i][j]);
-        }
+  for (int b = 0; b < 4; ++b) {
+    const int col = MODE == 0 ? min(n0 + 16 * (b & 1) + r16, m - 1) + (b >= 2 ? m : 0)
+                              : min(n0 + 16 * b + r16, d - 1);
+    bp[b] = Wexp + (size_t)col * Kdim;
+  }
+  auto load8 = [&](f32x4 (&v)[2], const float* p, int k) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int kk = k + 4 * h;
+      if constexpr (VEC) {
+        v[h] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (kk + 4 <= Kdim) v[h] = *reinterpret_cast<const f32x4*>(p + kk);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[h][e] = kk + e < Kdim ? p[kk + e] : 0.f;
       }
     }
-    __syncthreads();
+  };
+  auto load = [&](f32x4 (&a)[2][2], f32x4 (&b)[4][2], int c) {
+    const int k = c * FBK + 8 * q;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) load8(a[i], ap[i], k);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) load8(b[j], bp[j], k);
+  };
+  f32x4 acc[2][4];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int b = 0; b < 4; ++b) acc[i][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto mma = [&](const f32x4 (&a)[2][2], const f32x4 (&b)[4][2]) {
+#pragma unroll
+    for (int s = 0; s < 8; ++s)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][s >> 2][s & 3], b[j][s >> 2][s & 3], acc[i][j], 0, 0, 0);
+  };
+  const int nc = (Kdim + FBK - 1) / FBK;
+  f32x4 a0[2][2], b0[4][2], a1[2][2], b1[4][2];
+  int c = wv;
+  if (c < nc) load(a0, b0, c);
+  for (; c < nc; c += 8) {
+    if (c + 4 < nc) load(a1, b1, c + 4);
+    mma(a0, b0);
+    if (c + 4 >= nc) break;
+    if (c + 8 < nc) load(a0, b0, c + 8);
+    mma(a1, b1);
   }
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      int r = ty * 2 + i, col = nt * FBN + tx * 2 + j;
-      if (r < tile.rows && col < Ncols) {
-        float v = MODE == 0 ? silu_f(acc[0][i][j]) * acc[1][i][j] : acc[0][i][j];
-        C[(size_t)(tile.row0 + r) * Ncols + col] = v;
+    for (int b = 0; b < 4; ++b) part[wv][4 * i + b][lane] = acc[i][b];
+  __syncthreads();
+  // thread (w, lane): row block w / 2; gate/up: column block w % 2 of the
+  // gate and the up half; down: column blocks w % 2 and w % 2 + 2.  Lane l
+  // holds rows 4 (l / 16) .. + 3 of the block, column l % 16.
+  const int i = wv >> 1, b = wv & 1;
+  f32x4 v[2];
+#pragma unroll
+  for (int f = 0; f < 2; ++f) {
+    v[f] = part[0][4 * i + b + 2 * f][lane];
+#pragma unroll
+    for (int w = 1; w < 4; ++w) v[f] += part[w][4 * i + b + 2 * f][lane];
+  }
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const int r = 16 * i + 4 * q + t;
+    if (r >= wk.rows) continue;
+    float* dst = C + (size_t)(wk.row0 + r) * Ncols;
+    if (MODE == 0) {
+      const int col = n0 + 16 * b + r16;
+      if (col < Ncols) dst[col] = silu_f(v[0][t]) * v[1][t];
+    } else {
+#pragma unroll
+      for (int f = 0; f < 2; ++f) {
+        const int col = n0 + 16 * b + 32 * f + r16;
+        if (col < Ncols) dst[col] = v[f][t];
       }
     }
+  }
 }
 
 }  // namespace kern
 
 namespace {
 using kern::FBM;
-using kern::FBN;
+using kern::FBN0;
+using kern::FBN1;
 using kern::NTHR;
 using kern::Tiles;
 using kern::ffn_gemm_bf16_kernel;
@@ -1756,7 +1820,7 @@ int pick_bm(int rows_max, int E, bool packed) { return rows_max >= (packed ? 48 
 // n-tiles per GEMM.  bf16 weight-row tile: 512 when it divides the expert's
 // rows (gate/up: 2m, down: d), else 256 -- `wide` selects 512; the packed
 // kernel always runs 256-row tiles at two workgroups per CU.  float32: 32
-// output columns.
+// columns of h, 64 output columns.
 void n_tiles_of(bool bf16, bool packed, int d, int m, int& nn0, int& nn1, bool& wide0, bool& wide1) {
   if (bf16) {
     wide0 = !packed && (2 * m) % 512 == 0;
@@ -1765,8 +1829,8 @@ void n_tiles_of(bool bf16, bool packed, int d, int m, int& nn0, int& nn1, bool& 
     nn1 = d / (wide1 ? 512 : 256);
   } else {
     wide0 = wide1 = false;
-    nn0 = (m + FBN - 1) / FBN;
-    nn1 = (d + FBN - 1) / FBN;
+    nn0 = (m + FBN0 - 1) / FBN0;
+    nn1 = (d + FBN1 - 1) / FBN1;
   }
 }
 
@@ -1999,14 +2063,21 @@ hipError_t launch_expert_ffn(const void* x_perm, bool bf16, const int32_t* offse
     return launch_gemm(1, bm, wide1, t1, static_cast<const uint16_t*>(h),
                        static_cast<const uint16_t*>(w_down), static_cast<uint16_t*>(y_perm), d, m, s, g);
   }
-  ffn_gemm_f32_kernel<0><<<t0.max_tiles * nn0, NTHR, 0, s>>>(
-      static_cast<const float*>(x_perm), static_cast<const float*>(w_gate_up), static_cast<float*>(h),
-      t0, d, m, g);
+  const bool vec = d % 4 == 0 && m % 4 == 0;  // 16-byte rows (the arrays themselves are 16-byte aligned)
+  const int g0 = t0.max_tiles * nn0, g1 = t1.max_tiles * nn1;
+  auto xf = static_cast<const float*>(x_perm), wf = static_cast<const float*>(w_gate_up),
+       df = static_cast<const float*>(w_down);
+  auto hf = static_cast<float*>(h), yf = static_cast<float*>(y_perm);
+  if (vec)
+    ffn_gemm_f32_kernel<0, true><<<g0, NTHR, 0, s>>>(xf, wf, hf, t0, d, m, g);
+  else
+    ffn_gemm_f32_kernel<0, false><<<g0, NTHR, 0, s>>>(xf, wf, hf, t0, d, m, g);
   err = hipGetLastError();
   if (err != hipSuccess) return err;
-  ffn_gemm_f32_kernel<1><<<t1.max_tiles * nn1, NTHR, 0, s>>>(
-      static_cast<const float*>(h), static_cast<const float*>(w_down), static_cast<float*>(y_perm),
-      t1, d, m, g);
+  if (vec)
+    ffn_gemm_f32_kernel<1, true><<<g1, NTHR, 0, s>>>(hf, df, yf, t1, d, m, g);
+  else
+    ffn_gemm_f32_kernel<1, false><<<g1, NTHR, 0, s>>>(hf, df, yf, t1, d, m, g);
   return hipGetLastError();
 }
 

@@ -1265,6 +1265,33 @@ def test_few_rows_ffn(E, d, m, cnt, packed, monkeypatch):
         assert torch.equal(yp.view(torch.int16), y.view(torch.int16))
 
 
+# float32 tiles of 32 rows, 32 columns of h and 64 output columns, k in
+# 32-wide chunks over four wavefronts: one column more and less than a tile,
+# k shorter than a chunk, a chunk and a half, odd k (element loads), five and
+# nine chunks
+@pytest.mark.parametrize("E,d,m,cnt", [
+    (3, 64, 32, [1, 31, 32]),
+    (3, 68, 36, [33, 0, 65]),
+    (2, 63, 31, [5, 40]),
+    (2, 65, 33, [32, 2]),
+    (4, 160, 48, [0, 7, 64, 1]),
+    (2, 12, 288, [3, 30]),
+])
+def test_expert_ffn_f32_edges(E, d, m, cnt):
+    prm = I.layer_params(I.LayerShape(d=d, E=E, m=m, k=1, dtype="f32"), seed=d + m)
+    rows = sum(cnt)
+    offsets = dev(np.concatenate([[0], np.cumsum(cnt)]).astype(np.int32))
+    xp = dev(I.synthetic_rows(rows, d, "f32", seed=rows), torch.float32)
+    ws = torch.empty(abi.moe_workspace_size(rows, E, 1, d, m, 1), dtype=torch.uint8, device="cuda")
+    y = torch.full((rows + 1, d), 7.0, device="cuda")
+    abi.moe_expert_ffn(xp, offsets, dev(prm["w_gate_up"], torch.float32), dev(prm["w_down"], torch.float32),
+                       y[:rows], ws)
+    ref = oracle.expert_ffn_rows(host(xp), np.repeat(np.arange(E), cnt), prm["w_gate_up"], prm["w_down"])
+    assert rel_inf(host(y)[:rows], ref) <= TOL["f32"]
+    assert row_rel(host(y)[:rows], ref) <= TOL["f32"]
+    assert (host(y)[rows:] == 7.0).all()
+
+
 def test_expert_ffn_packed_gather_out_of_range_rows_read_token_zero():
     T, E, k, d, m = 64, 4, 2, 512, 256
     sh = I.LayerShape(d=d, E=E, m=m, k=k, dtype="bf16")
