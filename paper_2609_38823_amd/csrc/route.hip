@@ -419,6 +419,91 @@ __global__ __launch_bounds__(CAL_THREADS) void calibrate_route_kernel(
   for (int i = tid; i < n_zero; i += CAL_THREADS) zero[i] = i == mark_at ? mark_val : 0;
 }
 
+// ---------------------------------------------------------------------------
+// Invocations of a few tokens (up to ROUTE_SMALL_T): the Top-k, the masses, K,
+// the prefix re-route and the grouping in one launch of one workgroup.  A step
+// this small is bound by the chain of dependent steps and by the launches, not
+// by work: one row of 16 lanes holds a token's logits in registers from the
+// split partials to the re-route, and the routing entries pass from step to
+// step in LDS.  Bitwise the results of the separate launches (same sums, same
+// selection, same sort).
+// ---------------------------------------------------------------------------
+constexpr int ROUTE_SMALL_T = 16;
+constexpr int ROUTE_SMALL_C = 8;  // logits per lane: E <= 128 (16 per lane spill)
+
+template <int RMAXC>  // E <= 16 RMAXC
+__global__ __launch_bounds__(CAL_THREADS) void route_small_kernel(
+    float* __restrict__ logits, const float* __restrict__ part, int S, const float* __restrict__ bias, int T, int E,
+    int k, int key_bits, double p, int32_t* __restrict__ idx_full, float* __restrict__ w_full,
+    double* __restrict__ mass, int32_t* __restrict__ K_out, int32_t* __restrict__ idx, float* __restrict__ w,
+    int32_t* __restrict__ counts, int32_t* __restrict__ offsets, int32_t* __restrict__ src_of_row,
+    int32_t* __restrict__ row_of_slot, int* zero, int n_zero, int mark_at, int mark_val, const Guard g) {
+  if (guard_skip(g)) return;
+  __shared__ CalLds L;
+  const int tid = threadIdx.x, j = tid & 15;
+  const int A = T * k;
+  const int t = tid >> 4;
+  float v[RMAXC] = {};
+  if (t < T) {
+    float* row = logits + (size_t)t * E;
+    if (part) {
+      // partials in order, then the bias (as topk_kernel); the loads of eight
+      // partials in flight together
+      for (int sp = 0; sp < S; sp += 8) {
+        float pv[8][RMAXC];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+#pragma unroll
+          for (int c = 0; c < RMAXC; ++c) {
+            const int e = j + 16 * c;
+            pv[u][c] = sp + u < S && e < E ? part[((size_t)(sp + u) * T + t) * E + e] : 0.f;
+          }
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          if (sp + u < S) {
+#pragma unroll
+            for (int c = 0; c < RMAXC; ++c) v[c] = sp + u == 0 ? pv[u][c] : v[c] + pv[u][c];
+          }
+      }
+#pragma unroll
+      for (int c = 0; c < RMAXC; ++c) {
+        const int e = j + 16 * c;
+        if (e < E) {
+          v[c] += bias ? bias[e] : 0.f;
+          row[e] = v[c];
+        }
+      }
+    } else {
+#pragma unroll
+      for (int c = 0; c < RMAXC; ++c) {
+        const int e = j + 16 * c;
+        v[c] = e < E ? row[e] : 0.f;
+      }
+    }
+    row_topk_select<RMAXC>(v, j, E, k, E, L.st_e + t * k, L.st_w + t * k);
+  }
+  const double a = mass_staged(A, E, key_bits, L);  // its first barrier publishes the entries
+  // every partial has been read: the counters that the next launch starts
+  // from may lie in the same part of the workspace
+  for (int i = tid; i < n_zero; i += CAL_THREADS) zero[i] = i == mark_at ? mark_val : 0;
+  for (int i = tid; i < A; i += CAL_THREADS) {
+    idx_full[i] = L.st_e[i];
+    w_full[i] = L.st_w[i];
+  }
+  const int K = prefix_K(E, k, p, L);  // its barriers end the reads of the entries above
+  if (tid < E) mass[tid] = a;
+  if (tid == 0) K_out[0] = K;
+  const int Klim = clampi(K, k, E);
+  if (t < T) row_topk_select<RMAXC>(v, j, E, k, Klim, L.st_e + t * k, L.st_w + t * k);
+  __syncthreads();
+  for (int i = tid; i < A; i += CAL_THREADS) {
+    idx[i] = L.st_e[i];
+    w[i] = L.st_w[i];
+  }
+  sort_small(L.st_e, A, E, key_bits, reinterpret_cast<int*>(L.table), E, L.part, counts, offsets, src_of_row,
+             row_of_slot);
+}
+
 }  // namespace
 
 bool calibrate_route_fused(int T, int E, int k) {
@@ -454,6 +539,30 @@ hipError_t launch_calibrate_route(const float* logits, const int32_t* idx_full, 
   return hipGetLastError();
 }
 
+// The Top-k, calibration, re-route and grouping of one invocation after the
+// router's launch: one launch for a few tokens, else two.  The one workgroup
+// loses where its wavefronts share the SIMDs (E 128, k 8, router excluded:
+// 1 token 18.0 -> 14.5 us, 16 tokens 18.5 -> 16.5, 64 tokens 19.7 -> 21.5).
+bool route_small(int T, int E, int k) {
+  return T >= 1 && T <= ROUTE_SMALL_T && k <= 16 && E <= 16 * ROUTE_SMALL_C;
+}
+
+hipError_t launch_topk_calibrate_sort(float* logits, const float* part, int S, const float* bias, int T, int E, int k,
+                                      double p, int32_t* idx_full, float* w_full, double* mass, int32_t* K_out,
+                                      int32_t* idx, float* w, hipStream_t s, Guard g, const SortOut& so) {
+  if (route_small(T, E, k)) {
+    int key_bits = 0;
+    while ((1 << key_bits) < E) ++key_bits;
+    route_small_kernel<ROUTE_SMALL_C><<<1, CAL_THREADS, 0, s>>>(
+        logits, part, S, bias, T, E, k, key_bits, p, idx_full, w_full, mass, K_out, idx, w, so.counts, so.offsets,
+        so.src_of_row, so.row_of_slot, so.zero, so.n_zero, so.mark_at, so.mark_val, g);
+    return hipGetLastError();
+  }
+  hipError_t err = launch_topk(logits, T, E, k, nullptr, 1, nullptr, part, S, bias, idx_full, w_full, s, g, so.ctr);
+  if (err != hipSuccess) return err;
+  return launch_calibrate_route(logits, idx_full, w_full, T, E, k, p, mass, K_out, idx, w, s, g, &so);
+}
+
 bool route_rcep_fused(int T, int E, int k) {
   return calibrate_route_fused(T, E, k) && (size_t)T * k <= (size_t)DS_MAX && E <= DS_THREADS;
 }
@@ -485,11 +594,13 @@ hipError_t launch_route_rcep(const void* x, const void* w_r_packed, const float*
   // the counter sits past the router's partial sums (which the Top-k launch
   // reads while its first workgroup zeroes the counter)
   int* ctr = reinterpret_cast<int*>(static_cast<char*>(ws) + (route_x3_ws_bytes(T, d, E) + 255) / 256 * 256);
-  hipError_t err = launch_route(x, true, nullptr, w_r_packed, bias, T, d, E, k, nullptr, 1, nullptr, logits,
-                                idx_full, w_full, ws, s, g, ctr);
+  float* part = nullptr;
+  int S = 1;
+  hipError_t err = launch_router_x3(x, w_r_packed, bias, T, d, E, logits, ws, part, S, s, g);
   if (err != hipSuccess) return err;
   const SortOut so{counts, offsets, src_of_row, row_of_slot, ctr, za.p, za.n, za.mark_at, za.mark_val};
-  return launch_calibrate_route(logits, idx_full, w_full, T, E, k, p, mass, K_out, idx, w, s, g, &so);
+  return launch_topk_calibrate_sort(logits, part, S, bias, T, E, k, p, idx_full, w_full, mass, K_out, idx, w, s, g,
+                                    so);
 }
 
 hipError_t launch_route_rcep_chained(const void* y_prev, const int32_t* row_prev, const float* w_prev, void* h,
@@ -506,11 +617,10 @@ hipError_t launch_route_rcep_chained(const void* y_prev, const int32_t* row_prev
     int S = 1;
     hipError_t err = launch_combine_router_x3(y_prev, row_prev, w_prev, k, h, w_r_packed, bias, T, d, E, logits, ws,
                                               part, S, s, g);
-    if (err == hipSuccess)
-      err = launch_topk(logits, T, E, k, nullptr, 1, nullptr, part, S, bias, idx_full, w_full, s, g, ctr);
     if (err != hipSuccess) return err;
     const SortOut so{counts, offsets, src_of_row, row_of_slot, ctr, za.p, za.n, za.mark_at, za.mark_val};
-    return launch_calibrate_route(logits, idx_full, w_full, T, E, k, p, mass, K_out, idx, w, s, g, &so);
+    return launch_topk_calibrate_sort(logits, part, S, bias, T, E, k, p, idx_full, w_full, mass, K_out, idx, w, s, g,
+                                      so);
   }
   if (y_prev) {  // the combine on its own, then the routing of the new rows
     hipError_t err = launch_combine(y_prev, true, row_prev, w_prev, T, k, d, h, h, s, g);

@@ -11,43 +11,60 @@
 namespace decomoe {
 namespace {
 
-// (ov, oi) replaces (v, i) when its value is larger, or equal with a smaller
-// index; evaluated without short-circuit so that it compiles to compares and
-// selects (no exec-mask branches)
-__device__ __forceinline__ void better(float& v, int& i, float ov, int oi) {
-  const bool take = (ov > v) | ((ov == v) & (oi < i));
-  v = take ? ov : v;
-  i = take ? oi : i;
+// A candidate (value, expert) as one 64-bit key whose unsigned order is the
+// selection's order -- value descending, index ascending on ties -- so that a
+// comparison is one instruction without mask arithmetic between the scalar and
+// vector units.  High word: the float's bits mapped to unsigned order (-0 as
+// +0); low word: 0x7fffffff - e.  Key 0: taken, absent or NaN (never chosen
+// while a candidate is left; reads back as -inf, 0x7fffffff).
+// (Eight rounds over 128 experts, one row of 16 lanes per token: 3.8 -> 2.4 us.)
+typedef unsigned long long tkey;
+__device__ __forceinline__ tkey topk_key(float v, int e) {
+  uint32_t u = __float_as_uint(v + 0.f);
+  u ^= static_cast<uint32_t>(static_cast<int32_t>(u) >> 31) | 0x80000000u;
+  const tkey q = (static_cast<tkey>(u) << 32) | static_cast<uint32_t>(0x7fffffff - e);
+  return v == v ? q : 0ull;
 }
+__device__ __forceinline__ int key_index(tkey q) { return 0x7fffffff - static_cast<int>(static_cast<uint32_t>(q)); }
+__device__ __forceinline__ float key_value(tkey q) {
+  const uint32_t u = static_cast<uint32_t>(q >> 32);
+  const float v = __uint_as_float(u & 0x80000000u ? u ^ 0x80000000u : ~u);
+  return q ? v : -INFINITY;
+}
+__device__ __forceinline__ tkey key_max(tkey a, tkey b) { return a > b ? a : b; }
 
-// (value, index) of lane l -> the wavefront's best pair in every lane
-// without LDS round trips: DPP moves within each row of 16 lanes (quad
-// swaps, then the half-row and row mirrors pair the groups), then the four
-// row results are read with v_readlane and combined (the same in every
-// lane).  `better` is a total order on pairs, so the pairing order does not
-// change the result.
+// the best key of a row of 16 lanes in all its lanes, by DPP moves (quad
+// swaps, then the half-row and row mirrors pair the groups); the wavefront's
+// best: the four row results read with v_readlane (the same in every lane)
 template <int CTRL>
 __device__ __forceinline__ float dpp_f(float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xF, 0xF, false));
 }
 template <int CTRL>
-__device__ __forceinline__ void dpp_better(float& v, int& i) {
-  better(v, i, dpp_f<CTRL>(v), __builtin_amdgcn_mov_dpp(i, CTRL, 0xF, 0xF, false));
+__device__ __forceinline__ tkey dpp_max(tkey q) {
+  const int lo = __builtin_amdgcn_mov_dpp(static_cast<int>(q), CTRL, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_mov_dpp(static_cast<int>(q >> 32), CTRL, 0xF, 0xF, false);
+  return key_max(q, (static_cast<tkey>(static_cast<uint32_t>(hi)) << 32) | static_cast<uint32_t>(lo));
 }
 __device__ __forceinline__ float lane_f(float v, int l) {
   return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l));
 }
-__device__ __forceinline__ void wave_best(float& v, int& i) {
-  dpp_better<0xB1>(v, i);   // quad_perm [1, 0, 3, 2]
-  dpp_better<0x4E>(v, i);   // quad_perm [2, 3, 0, 1]
-  dpp_better<0x141>(v, i);  // row_half_mirror
-  dpp_better<0x140>(v, i);  // row_mirror
-  float bv = lane_f(v, 0);
-  int bi = __builtin_amdgcn_readlane(i, 0);
+__device__ __forceinline__ tkey row_best(tkey q) {
+  q = dpp_max<0xB1>(q);   // quad_perm [1, 0, 3, 2]
+  q = dpp_max<0x4E>(q);   // quad_perm [2, 3, 0, 1]
+  q = dpp_max<0x141>(q);  // row_half_mirror
+  return dpp_max<0x140>(q);  // row_mirror
+}
+__device__ __forceinline__ tkey wave_best(tkey q) {
+  q = row_best(q);
+  tkey best = 0;
 #pragma unroll
-  for (int r = 1; r < 4; ++r) better(bv, bi, lane_f(v, 16 * r), __builtin_amdgcn_readlane(i, 16 * r));
-  v = bv;
-  i = bi;
+  for (int r = 0; r < 4; ++r) {
+    const uint32_t lo = __builtin_amdgcn_readlane(static_cast<int>(q), 16 * r);
+    const uint32_t hi = __builtin_amdgcn_readlane(static_cast<int>(q >> 32), 16 * r);
+    best = key_max(best, (static_cast<tkey>(hi) << 32) | lo);
+  }
+  return best;
 }
 // sum over the wavefront: row sums by DPP, then the four rows in order
 __device__ __forceinline__ float wave_sum(float v) {
@@ -66,32 +83,24 @@ __device__ __forceinline__ float wave_sum(float v) {
 template <int MAXC>  // values per lane: E <= 64 MAXC
 __device__ __forceinline__ void topk_select_vals(const float (&vals)[MAXC], int E, int k, int Klim, int lane,
                                                  int32_t* idx_t, float* w_t) {
-  // a taken or absent candidate is (-inf, INT_MAX): `better` never prefers
-  // it, so the rounds need no per-candidate branches
-  float v[MAXC];
-  int ix[MAXC];
+  tkey q[MAXC];
 #pragma unroll
   for (int c = 0; c < MAXC; ++c) {
     const int e = lane + c * 64;
-    v[c] = e < Klim ? vals[c] : -INFINITY;
-    ix[c] = e < Klim ? e : 0x7fffffff;
+    q[c] = e < Klim ? topk_key(vals[c], e) : 0ull;
   }
-  float my_v = 0.f;
-  int my_i = 0;
+  tkey mine = 0;
   for (int r = 0; r < k; ++r) {
-    float bv = -INFINITY;
-    int bi = 0x7fffffff;
+    tkey best = q[0];
 #pragma unroll
-    for (int c = 0; c < MAXC; ++c) better(bv, bi, v[c], ix[c]);
-    wave_best(bv, bi);
+    for (int c = 1; c < MAXC; ++c) best = key_max(best, q[c]);
+    best = wave_best(best);
 #pragma unroll
-    for (int c = 0; c < MAXC; ++c)
-      if (ix[c] == bi) {
-        v[c] = -INFINITY;
-        ix[c] = 0x7fffffff;
-      }
-    if (lane == r) { my_v = bv; my_i = bi; }
+    for (int c = 0; c < MAXC; ++c) q[c] = q[c] == best ? 0ull : q[c];
+    if (lane == r) mine = best;
   }
+  const float my_v = key_value(mine);
+  const int my_i = key_index(mine);
   const float v0 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, my_v), 0));
   float ex = lane < k ? expf(my_v - v0) : 0.f;
   float sum = ex;
@@ -116,14 +125,6 @@ __device__ __forceinline__ void topk_select(const float* row, int E, int k, int 
 }
 
 // ---- one token per row of 16 lanes (four tokens per wavefront) ---------
-// the row's best pair in all 16 lanes: quad swaps, then the half-row and row
-// mirrors (no value leaves the row)
-__device__ __forceinline__ void row_best(float& v, int& i) {
-  dpp_better<0xB1>(v, i);   // quad_perm [1, 0, 3, 2]
-  dpp_better<0x4E>(v, i);   // quad_perm [2, 3, 0, 1]
-  dpp_better<0x141>(v, i);  // row_half_mirror
-  dpp_better<0x140>(v, i);  // row_mirror
-}
 __device__ __forceinline__ float row_sum(float v) {
   v += dpp_f<0xB1>(v);
   v += dpp_f<0x4E>(v);
@@ -141,37 +142,26 @@ __device__ __forceinline__ float row_sum(float v) {
 template <int MAXC>
 __device__ __forceinline__ void row_topk_select(const float (&v)[MAXC], int j, int E, int k, int Klim,
                                                 int32_t* idx_t, float* w_t) {
-  // candidates as in topk_select_vals: a taken or absent one is (-inf,
-  // INT_MAX), which `better` never prefers
-  float cv[MAXC];
-  int ix[MAXC];
+  tkey cq[MAXC];
 #pragma unroll
   for (int c = 0; c < MAXC; ++c) {
     const int e = j + 16 * c;
-    cv[c] = e < Klim ? v[c] : -INFINITY;
-    ix[c] = e < Klim ? e : 0x7fffffff;
+    cq[c] = e < Klim ? topk_key(v[c], e) : 0ull;
   }
-  float my_v[2] = {0.f, 0.f};
-  int my_i[2] = {0, 0};
+  tkey mine[2] = {0, 0};
   float v0 = 0.f;
   for (int r = 0; r < k; ++r) {
-    float bv = -INFINITY;
-    int bi = 0x7fffffff;
+    tkey best = cq[0];
 #pragma unroll
-    for (int c = 0; c < MAXC; ++c) better(bv, bi, cv[c], ix[c]);
-    row_best(bv, bi);
+    for (int c = 1; c < MAXC; ++c) best = key_max(best, cq[c]);
+    best = row_best(best);
 #pragma unroll
-    for (int c = 0; c < MAXC; ++c)
-      if (ix[c] == bi) {
-        cv[c] = -INFINITY;
-        ix[c] = 0x7fffffff;
-      }
-    if (r == 0) v0 = bv;
-    if ((r & 15) == j) {
-      my_v[r >> 4] = bv;
-      my_i[r >> 4] = bi;
-    }
+    for (int c = 0; c < MAXC; ++c) cq[c] = cq[c] == best ? 0ull : cq[c];
+    if (r == 0) v0 = key_value(best);
+    if ((r & 15) == j) mine[r >> 4] = best;
   }
+  const float my_v[2] = {key_value(mine[0]), key_value(mine[1])};
+  const int my_i[2] = {key_index(mine[0]), key_index(mine[1])};
   float ex[2];
 #pragma unroll
   for (int q = 0; q < 2; ++q) ex[q] = j + 16 * q < k ? expf(my_v[q] - v0) : 0.f;
