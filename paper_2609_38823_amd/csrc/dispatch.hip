@@ -11,7 +11,7 @@
 //                            rounds follow assignment order
 //   4. gather                each token row is read once and written to its
 //                            k dispatched rows with 16-byte stores
-// Up to 8192 assignments, steps 1-3 run in one workgroup (one launch); up
+// Up to DP_SORT_MAX assignments, steps 1-3 run in one workgroup (one launch); up
 // to 64 chunks, steps 2 and 3 run in one launch (every rank workgroup
 // re-derives the totals and its chunk's bases from the histograms).
 #include "common.hpp"
@@ -21,6 +21,9 @@ namespace decomoe {
 namespace {
 
 constexpr int DP_CHUNK = 1024;  // assignments per chunk
+// the one-workgroup sort up to here (8192: 8.6 us against 10), histogram and
+// ranks beyond (16 384: 14.3 us against 8.3)
+constexpr int DP_SORT_MAX = 8192;
 constexpr int DP_THREADS = 256;  // 4 wavefronts, 256 assignments each
 constexpr int DP_PER_WAVE = DP_CHUNK / (DP_THREADS / kWave);
 
@@ -265,7 +268,7 @@ __global__ __launch_bounds__(DP_THREADS) void dispatch_rank_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// Single-workgroup counting sort for up to DS_MAX assignments (one launch
+// Single-workgroup counting sort for up to DP_SORT_MAX assignments (one launch
 // instead of histogram + scan + rank): the 16 wavefronts take contiguous
 // slices in assignment order, count their slice per expert in LDS, one
 // scan turns the counts into offsets and each wavefront's starting row per
@@ -278,9 +281,9 @@ __global__ __launch_bounds__(DS_THREADS) void dispatch_sort_small_kernel(
     int32_t* __restrict__ row_of_slot, int* zero, int n_zero, int mark_at, int mark_val, const Guard g) {
   if (guard_skip(g)) return;
   zero_ints(zero, n_zero, mark_at, mark_val, DS_THREADS);
-  __shared__ int wh[DS_WAVES][1024];  // per-wave counts, then per-wave starting rows
+  __shared__ int wh[DS_WAVES * 1024];  // per-wave counts, then per-wave starting rows ([wave][E])
   __shared__ int part[DS_WAVES];
-  sort_small(idx, A, E, key_bits, &wh[0][0], 1024, part, counts, offsets, src_of_row, row_of_slot);
+  sort_small(idx, A, E, key_bits, wh, part, counts, offsets, src_of_row, row_of_slot);
 }
 
 // token-major gather: each token row is read once (VEC-sized vectors, rows
@@ -354,7 +357,7 @@ hipError_t launch_dispatch(const int32_t* idx, int T, int k, int E, const void* 
   int key_bits = 0;
   while ((1 << key_bits) < E) ++key_bits;
   hipError_t err;
-  if (A <= DS_MAX) {
+  if (A <= DP_SORT_MAX) {
     dispatch_sort_small_kernel<<<1, DS_THREADS, 0, s>>>(idx, A, E, key_bits, counts, offsets, src_of_row,
                                                         row_of_slot, za.p, za.n, za.mark_at, za.mark_val, g);
     err = hipGetLastError();

@@ -3,9 +3,9 @@
 // prefix re-route kernel.  Every function here is called by all
 // CAL_THREADS threads of the workgroup (they synchronise it).
 //
-//   mass_sorted   up to CAL_STAGE routing entries and E <= CAL_SORT_E: the
-//                 entries are staged with one bulk load and grouped by
-//                 expert with a stable counting sort in LDS (token order
+//   mass_sorted   up to CAL_SORT_A routing entries and E <= CAL_SORT_E: the
+//                 entries are loaded into registers and their weights grouped
+//                 by expert with a stable counting sort in LDS (token order
 //                 kept within an expert); thread e adds its expert's weights
 //                 in that order
 //   mass_chunked  larger invocations: chunks of tokens are scattered into a
@@ -19,6 +19,7 @@
 #pragma once
 
 #include "common.hpp"
+#include "sort_dev.hpp"
 
 namespace decomoe {
 namespace {
@@ -28,7 +29,8 @@ constexpr int CAL_TABLE = 8192;  // doubles in the LDS table (64 KB)
 constexpr int CAL_STAGE = 8192;  // routing entries staged per bulk load (64 KB)
 constexpr int CAL_ENT = 1024;    // routing entries scattered per chunk (one per thread)
 constexpr int CAL_WAVES = CAL_THREADS / kWave;
-constexpr int CAL_SORT_E = 512;  // the sorted path keeps [waves][E] counts in half the table
+constexpr int CAL_SORT_A = DS_MAX;  // routing entries of the sorted path
+constexpr int CAL_SORT_E = 512;  // the sorted path keeps [waves][E] counts in the table
 
 // Tokens per chunk: the table holds ch x E doubles and a chunk holds at most
 // CAL_ENT routing entries.
@@ -38,81 +40,37 @@ __host__ __device__ inline int cal_chunk(int E, int k) {
   return c < 64 ? c : 64;
 }
 
+static_assert(CAL_THREADS == DS_THREADS && CAL_SORT_A <= 2 * CAL_STAGE && CAL_WAVES * CAL_SORT_E <= 2 * CAL_TABLE,
+              "the sorted path's arrays fit");
 struct CalLds {
   double table[CAL_TABLE];
   double smass[1024 + 32];  // zero past E (the c_K loop reads whole batches)
-  int st_e[CAL_STAGE];
+  int st_e[CAL_STAGE];  // mass_sorted: with st_w the CAL_SORT_A grouped weights
   float st_w[CAL_STAGE];
-  int s_cnt[1024], s_off[1024];
   int part[CAL_WAVES];
-  double s_tot;
   int s_K;
 };
 
 // sets L.smass[e] = the mass of expert e (zero past E) and returns it in
-// thread e < E, from the n_all token-major entries staged in L.st_e and
-// L.st_w (the first barrier here publishes them)
-__device__ double mass_staged(int n_all, int E, int key_bits, CalLds& L) {
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  int* wh = reinterpret_cast<int*>(L.table);                                   // [waves][E]
-  float* sorted = reinterpret_cast<float*>(L.table) + CAL_WAVES * CAL_SORT_E;  // [CAL_STAGE]
-  for (int i = tid; i < CAL_WAVES * E; i += CAL_THREADS) wh[i] = 0;
-  __syncthreads();
-  const int per = ((n_all + CAL_WAVES - 1) / CAL_WAVES + kWave - 1) / kWave * kWave;
-  const int a_lo = min(n_all, wv * per), a_hi = min(n_all, a_lo + per);
-  for (int a = a_lo + lane; a < a_hi; a += kWave) {
-    const int e = L.st_e[a];
-    if (e >= 0 && e < E) atomicAdd(&wh[wv * E + e], 1);
-  }
-  __syncthreads();
-  int cnt = 0;
-  if (tid < E)
-    for (int q = 0; q < CAL_WAVES; ++q) cnt += wh[q * E + tid];
-  int incl = cnt;
-#pragma unroll
-  for (int off = 1; off < kWave; off <<= 1) {
-    const int y = __shfl_up(incl, off, kWave);
-    if (lane >= off) incl += y;
-  }
-  if (lane == kWave - 1) L.part[wv] = incl;
-  __syncthreads();
-  if (tid < E) {
-    int r = incl - cnt;
-    for (int q = 0; q < wv; ++q) r += L.part[q];
-    L.s_cnt[tid] = cnt;
-    L.s_off[tid] = r;
-    for (int q = 0; q < CAL_WAVES; ++q) {  // per-wave starting positions
-      const int c = wh[q * E + tid];
-      wh[q * E + tid] = r;
-      r += c;
-    }
-  }
-  __syncthreads();
-  const uint64_t lt_mask = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-  for (int a0 = a_lo; a0 < a_hi; a0 += kWave) {
-    const int a = a0 + lane;
-    const int e = a < a_hi ? L.st_e[a] : -1;
-    const bool valid = e >= 0 && e < E;
-    uint64_t peers = __ballot(valid);
-    for (int b = 0; b < key_bits; ++b) {
-      const bool bit = (e >> b) & 1;
-      const uint64_t msk = __ballot(bit);
-      peers &= bit ? msk : ~msk;
-    }
-    if (valid) {
-      sorted[wh[wv * E + e] + __popcll(peers & lt_mask)] = L.st_w[a];
-      if ((63 - __clzll(peers)) == lane) wh[wv * E + e] += __popcll(peers);
-    }
-    __builtin_amdgcn_wave_barrier();
-  }
+// thread e < E, from this thread's entries (key, weight) in the slices of
+// sort_dev.hpp; `sorted` (LDS) holds the weights grouped by expert
+template <int R>
+__device__ __forceinline__ double mass_of_entries(const int (&key)[R], const float (&rw)[R], int nr, int E,
+                                                  int key_bits, float* sorted, CalLds& L) {
+  const int tid = threadIdx.x, wv = tid >> 6;
+  int* wh = reinterpret_cast<int*>(L.table);  // [waves][E]
+  int cnt, first;
+  slice_scan<R>(key, nr, E, wh, E, L.part, cnt, first);
+  rank_rounds<R>(key, nr, E, key_bits, wh + wv * E, [&](int r, int pos, int) {
+    if (pos >= 0) sorted[pos] = rw[r];
+  });
   __syncthreads();
   double a = 0.0;
   if (tid < E) {
     // one dependent float64 chain per expert (the latency of the
     // additions, not of the LDS reads, bounds it)
-    const int b0 = L.s_off[tid], b1 = b0 + L.s_cnt[tid];
 #pragma unroll 8
-    for (int j = b0; j < b1; ++j) a += static_cast<double>(sorted[j]);
+    for (int j = first; j < first + cnt; ++j) a += static_cast<double>(sorted[j]);
     L.smass[tid] = a;
   } else {
     L.smass[tid] = 0.0;
@@ -122,29 +80,27 @@ __device__ double mass_staged(int n_all, int E, int key_bits, CalLds& L) {
   return a;
 }
 
-// the same for the n_all routing entries from idx + base (token-major)
+// the same for the n_all routing entries from idx + base (token-major), each
+// wavefront loading its own slice into registers
 __device__ double mass_sorted(const int32_t* __restrict__ idx, const float* __restrict__ w, size_t base,
                               int n_all, int E, int key_bits, CalLds& L) {
-  const int tid = threadIdx.x;
-  {
-    constexpr int SPT = CAL_STAGE / CAL_THREADS;
-    int re[SPT];
-    float rw[SPT];
+  const int lane = threadIdx.x & 63;
+  const int nr = slice_rounds(n_all), lo = slice_lo(n_all, nr), hi = min(n_all, lo + nr * kWave);
+  double mass = 0.0;
+  with_rounds(nr, [&](auto RC) {
+    constexpr int R = decltype(RC)::value;
+    int key[R];
+    float rw[R];
 #pragma unroll
-    for (int q = 0; q < SPT; ++q) {
-      const int i = tid + q * CAL_THREADS;
-      re[q] = i < n_all ? idx[base + i] : -1;
-      rw[q] = i < n_all ? w[base + i] : 0.f;
+    for (int r = 0; r < R; ++r) {
+      const int a = lo + r * kWave + lane;
+      const bool in = r < nr && a < hi;
+      key[r] = in ? idx[base + a] : -1;
+      rw[r] = in ? w[base + a] : 0.f;
     }
-#pragma unroll
-    for (int q = 0; q < SPT; ++q) {  // only entries below n_all are read below
-      if (tid + q * CAL_THREADS < n_all) {
-        L.st_e[tid + q * CAL_THREADS] = re[q];
-        L.st_w[tid + q * CAL_THREADS] = rw[q];
-      }
-    }
-  }
-  return mass_staged(n_all, E, key_bits, L);
+    mass = mass_of_entries<R>(key, rw, nr, E, key_bits, reinterpret_cast<float*>(L.st_e), L);
+  });
+  return mass;
 }
 
 // the same for the tokens [lo, hi), any size

@@ -340,7 +340,7 @@ __global__ __launch_bounds__(256) void topk_row_kernel(float* __restrict__ logit
 // Calibration and prefix re-route of one invocation in one launch (Eqs. 11,
 // 12, then the re-route of Sec. 3.3).  Every workgroup forms the masses and
 // K itself -- the same float64 sums as segment_mass_kernel (mass_sorted,
-// prefix_K), over at most CAL_STAGE routing entries -- so no second launch
+// prefix_K), over at most CAL_SORT_A routing entries -- so no second launch
 // waits for one workgroup's result; workgroup 0 writes mass and K.  Then
 // workgroup b re-routes the tokens 16 b .. 16 b + 15 (stride 16 x grid)
 // inside [0, K) with the selection of topk_kernel: for k <= 16 and E <= 16
@@ -413,7 +413,7 @@ __global__ __launch_bounds__(CAL_THREADS) void calibrate_route_kernel(
   }
   __syncthreads();
   if (!s_last) return;
-  sort_small(idx, T * k, E, key_bits, reinterpret_cast<int*>(L.table), E, L.part, counts, offsets, src_of_row,
+  sort_small(idx, T * k, E, key_bits, reinterpret_cast<int*>(L.table), L.part, counts, offsets, src_of_row,
              row_of_slot);
   // every other workgroup is done with the workspace
   for (int i = tid; i < n_zero; i += CAL_THREADS) zero[i] = i == mark_at ? mark_val : 0;
@@ -482,9 +482,12 @@ __global__ __launch_bounds__(CAL_THREADS) void route_small_kernel(
     }
     row_topk_select<RMAXC>(v, j, E, k, E, L.st_e + t * k, L.st_w + t * k);
   }
-  const double a = mass_staged(A, E, key_bits, L);  // its first barrier publishes the entries
-  // every partial has been read: the counters that the next launch starts
-  // from may lie in the same part of the workspace
+  __syncthreads();  // the entries are in LDS; every partial has been read
+  const int ea = tid < A ? L.st_e[tid] : -1;
+  const double a = mass_of_entries<1>({ea}, {tid < A ? L.st_w[tid] : 0.f}, 1, E, key_bits,
+                                      reinterpret_cast<float*>(L.table) + CAL_WAVES * 16 * ROUTE_SMALL_C, L);
+  // the counters that the next launch starts from may lie where the partials
+  // were
   for (int i = tid; i < n_zero; i += CAL_THREADS) zero[i] = i == mark_at ? mark_val : 0;
   for (int i = tid; i < A; i += CAL_THREADS) {
     idx_full[i] = L.st_e[i];
@@ -500,14 +503,17 @@ __global__ __launch_bounds__(CAL_THREADS) void route_small_kernel(
     idx[i] = L.st_e[i];
     w[i] = L.st_w[i];
   }
-  sort_small(L.st_e, A, E, key_bits, reinterpret_cast<int*>(L.table), E, L.part, counts, offsets, src_of_row,
-             row_of_slot);
+  sort_rounds<1>(L.st_e, A, E, key_bits, reinterpret_cast<int*>(L.table), L.part, counts, offsets, src_of_row,
+                 row_of_slot);
 }
 
 }  // namespace
 
+// One launch up to CAL_SORT_A entries, the grouping's sort by its last
+// workgroup included (12 248 entries, E 128: 36 us, where masses, re-route,
+// histogram, ranks and the FFN's clearing launch took 68).
 bool calibrate_route_fused(int T, int E, int k) {
-  return T >= 1 && (size_t)T * k <= (size_t)CAL_STAGE && E <= CAL_SORT_E;
+  return T >= 1 && (size_t)T * k <= (size_t)CAL_SORT_A && E <= CAL_SORT_E;
 }
 
 hipError_t launch_calibrate_route(const float* logits, const int32_t* idx_full, const float* w_full,
@@ -568,11 +574,12 @@ bool route_rcep_fused(int T, int E, int k) {
 }
 
 size_t route_rcep_ws_bytes(int T, int d, int E, int k) {
-  if (!route_rcep_fused(T, E, k)) {
-    const size_t a = route_x3_ws_bytes(T, d, E), b = dispatch_ws_bytes(T, k, E);
-    return a > b ? a : b;
-  }
-  return (route_x3_ws_bytes(T, d, E) + 255) / 256 * 256 + 256;  // + the completion counter
+  const size_t a = route_x3_ws_bytes(T, d, E);
+  // up to 8192 entries nothing but the partials is written; the 256 bytes
+  // more are part of the call's contract, and so is the dispatch's part above
+  if (T >= 1 && (size_t)T * k <= 8192 && E <= CAL_SORT_E) return (a + 255) / 256 * 256 + 256;
+  const size_t b = dispatch_ws_bytes(T, k, E);
+  return a > b ? a : b;
 }
 
 hipError_t launch_route_rcep(const void* x, const void* w_r_packed, const float* bias, int T, int d, int E,
@@ -591,9 +598,8 @@ hipError_t launch_route_rcep(const void* x, const void* w_r_packed, const float*
                             s, g);
     return err;
   }
-  // the counter sits past the router's partial sums (which the Top-k launch
-  // reads while its first workgroup zeroes the counter)
-  int* ctr = reinterpret_cast<int*>(static_cast<char*>(ws) + (route_x3_ws_bytes(T, d, E) + 255) / 256 * 256);
+  // counts[0] counts the finished workgroups until the last one sorts
+  int* ctr = counts;
   float* part = nullptr;
   int S = 1;
   hipError_t err = launch_router_x3(x, w_r_packed, bias, T, d, E, logits, ws, part, S, s, g);
@@ -612,7 +618,7 @@ hipError_t launch_route_rcep_chained(const void* y_prev, const int32_t* row_prev
   if (y_prev && combine_router_fits(T, d, E, k) && route_rcep_fused(T, E, k)) {
     // the previous combine inside the router launch, then the Top-k (which
     // zeroes the grouping's counter) and the one-launch calibration
-    int* ctr = reinterpret_cast<int*>(static_cast<char*>(ws) + (route_x3_ws_bytes(T, d, E) + 255) / 256 * 256);
+    int* ctr = counts;  // as in launch_route_rcep
     float* part = nullptr;
     int S = 1;
     hipError_t err = launch_combine_router_x3(y_prev, row_prev, w_prev, k, h, w_r_packed, bias, T, d, E, logits, ws,

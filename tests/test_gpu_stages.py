@@ -542,6 +542,16 @@ D256_E256_K20 = I.LayerShape(d=256, E=256, m=256, k=20, dtype="bf16", zipf_alpha
 RCEP_LAYER_SHAPES = {"qwen": I.QWEN3_VL_MOE, "e64": D256_E64, "e256k20": D256_E256_K20}
 
 
+# edges of the routing launches: the one-workgroup launch up to 16 tokens, the
+# one-launch calibration and grouping up to 16384 entries (slices of one, four
+# and sixteen rounds per wavefront), the separate launches beyond
+@pytest.mark.parametrize("shape,T", [("qwen", 2), ("qwen", 16), ("qwen", 17), ("qwen", 128), ("qwen", 129),
+                                     ("qwen", 513), ("qwen", 1531), ("qwen", 2048), ("qwen", 2049), ("d64", 16),
+                                     ("e96", 15), ("e256", 16), ("e256k20", 9)])
+def test_route_rcep_launch_edges(shape, T):
+    test_route_rcep_matches_separate_calls(shape, T)
+
+
 class _RcepLayer:
     """Weights of one shape and the outputs of one call."""
 
