@@ -3,13 +3,16 @@
 //
 //   pool     the n - 1 preceding text rows are summed per column in float32,
 //            rows split over blockIdx.y (each split sums its rows in order)
-//   feature  x = [sum / (n - 1); row n - 1] (the splits added in order,
-//            then one scaling), one column per thread
-//   hidden   every workgroup loads x into LDS and each wavefront forms one
-//            hidden unit relu(W1[u] . x + b1[u])
-//   decide   one workgroup: the two class logits, p_exit = softmax(z)_1 and
-//            the exit flag p_exit >= theta (compared in float64)
-// Every sum has a fixed order, so the gate is deterministic.
+//   mlp      every workgroup forms the feature x = [sum / (n - 1); row n - 1]
+//            in LDS (the splits added in order, then one scaling) while its
+//            first weights are on their way, and each wavefront one hidden
+//            unit relu(W1[u] . x + b1[u]); the last workgroup to finish forms
+//            the two class logits, p_exit = softmax(z)_1 and the exit flag
+//            p_exit >= theta (compared in float64)
+// Every sum has a fixed order, so the gate is deterministic.  The gate is
+// bound by its launches and their dependent loads: two launches instead of
+// four (feature and decision on their own): gate over 512 rows, d 2048, 512
+// hidden units, and the drop behind it: 32.5 -> 26.5 us.
 #include "common.hpp"
 
 namespace decomoe {
@@ -27,8 +30,10 @@ int savb_splits(int n) {
 // partial[s][c] = sum of rows [s*per, (s+1)*per) of column c (rows < n - 1)
 template <bool BF16>
 __global__ __launch_bounds__(256) void savb_pool_kernel(const void* __restrict__ rows, int n, int d,
-                                                        int per, float* __restrict__ partial, const Guard g) {
+                                                        int per, float* __restrict__ partial, int* __restrict__ ctr, const Guard g) {
   if (guard_skip(g)) return;
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *ctr = 0;  // the workgroups the next launch finishes
+  if (n < 2) return;  // no preceding rows
   const int c = blockIdx.x * 256 + threadIdx.x;
   if (c >= d) return;
   const int r0 = blockIdx.y * per, r1 = min(n - 1, r0 + per);
@@ -49,87 +54,121 @@ __global__ __launch_bounds__(256) void savb_pool_kernel(const void* __restrict__
   partial[(size_t)blockIdx.y * d + c] = acc;
 }
 
-// x[c] = (sum of the splits' partials, in split order) / (n - 1) and
-// x[d + c] = text row n - 1, one column per thread; the partial loads of a
-// column are all issued before the additions
+// the value of text row n - 1 at column c
 template <bool BF16>
-__global__ __launch_bounds__(256) void savb_feature_kernel(const void* __restrict__ rows, int n, int d,
-                                                           int splits, const float* __restrict__ partial,
-                                                           float* __restrict__ x, const Guard g) {
-  if (guard_skip(g)) return;
-  const int c = blockIdx.x * 256 + threadIdx.x;
-  if (c >= d) return;
-  float v[16];
-#pragma unroll
-  for (int q = 0; q < 16; ++q) v[q] = q < splits ? partial[(size_t)q * d + c] : 0.f;
-  float s = 0.f;
-#pragma unroll
-  for (int q = 0; q < 16; ++q)
-    if (q < splits) s += v[q];
-  x[c] = n > 1 ? s * (1.f / static_cast<float>(n - 1)) : 0.f;
-  x[d + c] = BF16 ? bf16_to_f32(static_cast<const uint16_t*>(rows)[(size_t)(n - 1) * d + c])
-                  : static_cast<const float*>(rows)[(size_t)(n - 1) * d + c];
+__device__ __forceinline__ float last_row(const void* rows, int n, int d, int c) {
+  return BF16 ? bf16_to_f32(static_cast<const uint16_t*>(rows)[(size_t)(n - 1) * d + c])
+              : static_cast<const float*>(rows)[(size_t)(n - 1) * d + c];
 }
 
-// x into LDS, then wavefront w of block b computes hidden unit 4 b + w
-__global__ __launch_bounds__(256) void savb_hidden_kernel(const float* __restrict__ x, int d,
-                                                          const float* __restrict__ w1,
-                                                          const float* __restrict__ b1, int hid,
-                                                          float* __restrict__ hidden, const Guard g) {
+template <bool BF16>
+__global__ __launch_bounds__(256) void savb_mlp_kernel(
+    const void* __restrict__ rows, int n, int d, int splits, const float* __restrict__ partial,
+    float* __restrict__ feature, const float* __restrict__ w1, const float* __restrict__ b1, int hid,
+    float* __restrict__ hidden, const float* __restrict__ w2, const float* __restrict__ b2, double theta,
+    float* __restrict__ p_exit, int32_t* __restrict__ exit_flag, int32_t* __restrict__ exit_layer, int layer,
+    int* __restrict__ ctr, const Guard g) {
   if (guard_skip(g)) return;
-  extern __shared__ float xs[];  // [2d]
-  for (int c = threadIdx.x; c < 2 * d; c += 256) xs[c] = x[c];
-  __syncthreads();
-  const int lane = threadIdx.x & 63;
-  const int u = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (u >= hid) return;
-  const float* wr = w1 + (size_t)u * 2 * d;
-  float acc = 0.f;
-  if ((d & 127) == 0 && (reinterpret_cast<uintptr_t>(wr) & 15) == 0) {
-    // 16-byte loads, eight in flight per lane: lane l takes columns
-    // 4 (l + 64 j) .. + 4 for j = 0, 1, ...
-    const float4* w4 = reinterpret_cast<const float4*>(wr);
-    const int n4 = (2 * d) >> 2;
-    for (int j0 = lane; j0 < n4; j0 += 64 * 8) {
-      float4 v[8];
+  extern __shared__ __attribute__((aligned(16))) float xs[];  // [2d], 64 KB at d = 8192: the last steps reuse it
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int u = blockIdx.x * 4 + wv;
+  const float* wr = w1 + (size_t)min(u, hid - 1) * 2 * d;
+  // 16-byte weight loads: lane l takes columns 4 (l + 64 j) .. + 4 for j = 0,
+  // 1, ...; the first PRE of them are issued before x is formed
+  constexpr int PRE = 16;
+  const bool vec = (d & 127) == 0 && (reinterpret_cast<uintptr_t>(wr) & 15) == 0;
+  const float4* w4 = reinterpret_cast<const float4*>(wr);
+  const int n4 = (2 * d) >> 2;
+  float4 v[PRE];
 #pragma unroll
-      for (int u8 = 0; u8 < 8; ++u8) v[u8] = j0 + 64 * u8 < n4 ? w4[j0 + 64 * u8] : make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int q = 0; q < PRE; ++q) {
+    const int j = lane + 64 * q;
+    v[q] = vec && j < n4 ? w4[j] : make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+  const float inv = n > 1 ? 1.f / static_cast<float>(n - 1) : 0.f;
+  if ((d & 3) == 0) {  // the partials' rows are whole 16-byte vectors (the workspace is 16-byte aligned)
+    for (int c = 4 * tid; c < d; c += 1024) {
+      float4 pv[16];
 #pragma unroll
-      for (int u8 = 0; u8 < 8; ++u8) {
-        const int c = 4 * (j0 + 64 * u8);
-        if (j0 + 64 * u8 < n4) {
-          acc = fmaf(v[u8].x, xs[c], acc);
-          acc = fmaf(v[u8].y, xs[c + 1], acc);
-          acc = fmaf(v[u8].z, xs[c + 2], acc);
-          acc = fmaf(v[u8].w, xs[c + 3], acc);
+      for (int q = 0; q < 16; ++q)
+        pv[q] = q < splits ? *reinterpret_cast<const float4*>(partial + (size_t)q * d + c)
+                           : make_float4(0.f, 0.f, 0.f, 0.f);
+      float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+      for (int q = 0; q < 16; ++q)
+        if (q < splits) {
+          s.x += pv[q].x;
+          s.y += pv[q].y;
+          s.z += pv[q].z;
+          s.w += pv[q].w;
         }
-      }
+      *reinterpret_cast<float4*>(xs + c) = n > 1 ? make_float4(s.x * inv, s.y * inv, s.z * inv, s.w * inv)
+                                                 : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) xs[d + c + e] = last_row<BF16>(rows, n, d, c + e);
     }
   } else {
-    for (int c = lane; c < 2 * d; c += 64) acc = fmaf(wr[c], xs[c], acc);
+    for (int c = tid; c < d; c += 256) {
+      float s = 0.f;
+      for (int q = 0; q < splits; ++q) s += partial[(size_t)q * d + c];
+      xs[c] = n > 1 ? s * inv : 0.f;
+      xs[d + c] = last_row<BF16>(rows, n, d, c);
+    }
   }
-  // lanes in order: the sum of lane partials is formed by lane 0
-  for (int off = 32; off >= 1; off >>= 1) acc += __shfl_down(acc, off, 64);
-  if (lane == 0) hidden[u] = fmaxf(acc + (b1 ? b1[u] : 0.f), 0.f);
-}
-
-// two wavefronts: class c = wavefront c; then thread 0 decides
-__global__ __launch_bounds__(128) void savb_decide_kernel(const float* __restrict__ hidden, int hid,
-                                                          const float* __restrict__ w2,
-                                                          const float* __restrict__ b2, double theta,
-                                                          float* __restrict__ p_exit,
-                                                          int32_t* __restrict__ exit_flag,
-                                                          int32_t* __restrict__ exit_layer, int layer,
-                                                          const Guard g) {
-  if (guard_skip(g)) return;
-  __shared__ float z[2];
-  const int lane = threadIdx.x & 63, cls = threadIdx.x >> 6;
-  float acc = 0.f;
-  for (int u = lane; u < hid; u += 64) acc = fmaf(w2[(size_t)cls * hid + u], hidden[u], acc);
-  for (int off = 32; off >= 1; off >>= 1) acc += __shfl_down(acc, off, 64);
-  if (lane == 0) z[cls] = acc + (b2 ? b2[cls] : 0.f);
   __syncthreads();
-  if (threadIdx.x == 0) {
+  if (feature && blockIdx.x == 0)
+    for (int c = tid; c < 2 * d; c += 256) feature[c] = xs[c];
+  if (u < hid) {
+    float acc = 0.f;
+    auto add4 = [&](const float4& w, int j) {
+      const float4 x = *reinterpret_cast<const float4*>(xs + 4 * j);
+      acc = fmaf(w.x, x.x, acc);
+      acc = fmaf(w.y, x.y, acc);
+      acc = fmaf(w.z, x.z, acc);
+      acc = fmaf(w.w, x.w, acc);
+    };
+    if (vec) {
+#pragma unroll
+      for (int q = 0; q < PRE; ++q)
+        if (lane + 64 * q < n4) add4(v[q], lane + 64 * q);
+      for (int j0 = lane + 64 * PRE; j0 < n4; j0 += 64 * 8) {  // eight loads in flight
+        float4 r[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) r[q] = j0 + 64 * q < n4 ? w4[j0 + 64 * q] : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+          if (j0 + 64 * q < n4) add4(r[q], j0 + 64 * q);
+      }
+    } else {
+      for (int c = lane; c < 2 * d; c += 64) acc = fmaf(wr[c], xs[c], acc);
+    }
+    // lanes in order: the sum of lane partials is formed by lane 0
+    for (int off = 32; off >= 1; off >>= 1) acc += __shfl_down(acc, off, 64);
+    // agent scope: the deciding workgroup may run on another XCD
+    if (lane == 0)
+      __hip_atomic_store(hidden + u, fmaxf(acc + (b1 ? b1[u] : 0.f), 0.f), __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
+  }
+  // every unit of the workgroup is stored (vmcnt 0), then it counts itself;
+  // the last one decides
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  if (tid == 0)
+    xs[0] = __hip_atomic_fetch_add(ctr, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
+  __syncthreads();
+  if (xs[0] == 0.f) return;
+  __syncthreads();
+  float* z = xs;
+  if (wv < 2) {  // class = wavefront
+    float acc = 0.f;
+    for (int h = lane; h < hid; h += 64)
+      acc = fmaf(w2[(size_t)wv * hid + h],
+                 __hip_atomic_load(hidden + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), acc);
+    for (int off = 32; off >= 1; off >>= 1) acc += __shfl_down(acc, off, 64);
+    if (lane == 0) z[wv] = acc + (b2 ? b2[wv] : 0.f);
+  }
+  __syncthreads();
+  if (tid == 0) {
     const float mx = fmaxf(z[0], z[1]);
     const float e0 = expf(z[0] - mx), e1 = expf(z[1] - mx);
     const float p = e1 / (e0 + e1);
@@ -178,31 +217,23 @@ hipError_t launch_savb_gate(const void* rows, bool bf16, int n, int d, const flo
   const int splits = savb_splits(n);
   float* partial = static_cast<float*>(ws);
   float* hidden = partial + (size_t)splits * d;
-  if (splits > 0) {
-    const dim3 grid((d + 255) / 256, splits);
-    const int per = (n - 1 + splits - 1) / splits;  // rows per split (splits * per >= n - 1)
-    if (bf16)
-      savb_pool_kernel<true><<<grid, 256, 0, s>>>(rows, n, d, per, partial, g);
-    else
-      savb_pool_kernel<false><<<grid, 256, 0, s>>>(rows, n, d, per, partial, g);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  float* x = hidden + hid;  // the feature (also the caller's copy when given)
-  if (feature) x = feature;
-  const unsigned fb = (unsigned)((d + 255) / 256);
+  int* ctr = reinterpret_cast<int*>(hidden + hid);
+  const dim3 grid(splits > 0 ? (d + 255) / 256 : 1, splits > 0 ? splits : 1);
+  const int per = splits > 0 ? (n - 1 + splits - 1) / splits : 0;  // rows per split (splits * per >= n - 1)
   if (bf16)
-    savb_feature_kernel<true><<<fb, 256, 0, s>>>(rows, n, d, splits, partial, x, g);
+    savb_pool_kernel<true><<<grid, 256, 0, s>>>(rows, n, d, per, partial, ctr, g);
   else
-    savb_feature_kernel<false><<<fb, 256, 0, s>>>(rows, n, d, splits, partial, x, g);
+    savb_pool_kernel<false><<<grid, 256, 0, s>>>(rows, n, d, per, partial, ctr, g);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const unsigned hb = (unsigned)((hid + 3) / 4);
   const size_t lds = (size_t)2 * d * sizeof(float);
-  savb_hidden_kernel<<<hb, 256, lds, s>>>(x, d, w1, b1, hid, hidden, g);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  savb_decide_kernel<<<1, 128, 0, s>>>(hidden, hid, w2, b2, theta, p_exit, exit_flag, exit_layer, layer, g);
+  if (bf16)
+    savb_mlp_kernel<true><<<hb, 256, lds, s>>>(rows, n, d, splits, partial, feature, w1, b1, hid, hidden, w2, b2,
+                                               theta, p_exit, exit_flag, exit_layer, layer, ctr, g);
+  else
+    savb_mlp_kernel<false><<<hb, 256, lds, s>>>(rows, n, d, splits, partial, feature, w1, b1, hid, hidden, w2, b2,
+                                                theta, p_exit, exit_flag, exit_layer, layer, ctr, g);
   return hipGetLastError();
 }
 

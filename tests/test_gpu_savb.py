@@ -77,6 +77,24 @@ def test_savb_gate(n, d, dt):
     assert abs(p - p_free) <= 1e-4
 
 
+# the feature in LDS (64 KB at d = 8192), vector and element loads of the
+# weights and partials, weights beyond the first 16 loads of a lane, one
+# hidden unit, a last workgroup that is not full, no preceding rows
+@pytest.mark.parametrize("n,d,hid,dt", [(3, 8192, 5, "bf16"), (40, 2176, 1, "f32"), (1, 128, 7, "bf16"),
+                                        (70, 3, 9, "f32"), (2, 1, 1, "f32"), (33, 100, 600, "bf16")])
+def test_savb_gate_edges(n, d, hid, dt):
+    rng = np.random.default_rng(n + d + hid)
+    rows = I.synthetic_rows(n, d, dt, seed=d)
+    gp = {k: (rng.standard_normal(s) * 0.05).astype(np.float32)
+          for k, s in (("w1", (hid, 2 * d)), ("b1", (hid,)), ("w2", (2, hid)), ("b2", (2,)))}
+    p_ref = oracle.savb_gate(rows, gp["w1"], gp["b1"], gp["w2"], gp["b2"], 0.5)[0]
+    for _ in range(2):
+        feat, p, flag = run_gate(rows, dt, gp, p_ref - 1e-3)
+        assert np.abs(feat - oracle.savb_gate_feature(rows)).max() <= 1e-5 * max(np.abs(feat).max(), 1.0)
+        assert abs(p - p_ref) <= 1e-4 and flag == 1
+    assert run_gate(rows, dt, gp, p_ref + 1e-3)[2] == 0
+
+
 def test_savb_gate_deterministic():
     rows = I.tokens(I.QWEN3_VL_MOE, 512, seed=3)
     gp = I.gate_params(2048, seed=1)
