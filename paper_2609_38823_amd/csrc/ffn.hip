@@ -62,6 +62,22 @@ struct Tiles {
 
 constexpr int NTHR = 256;  // threads per GEMM workgroup (4 wavefronts)
 
+constexpr int FFN_MAXE = 1024;
+constexpr int FFN_CTR_TILES = 128;  // ctr index of done[0] (see the persistent kernel)
+constexpr int FFN_CTR_PATH = 5;     // in XCD 0's block: the call's launch path
+
+// Kernels that use no counters: the first workgroup of the call's first launch
+// writes the counter header that moe_ffn_status reads (zeros and the path), so
+// the call needs no clearing launch.  ctr = NULL: nothing to write.
+struct Header {
+  int* ctr;
+  int path;
+};
+__device__ __forceinline__ void write_header(const Header& h) {
+  if (h.ctr && blockIdx.x == 0 && threadIdx.x < FFN_CTR_TILES)
+    h.ctr[threadIdx.x] = threadIdx.x == FFN_CTR_PATH ? h.path : 0;
+}
+
 // Fills `out` with work item L and returns true, or returns false (for the
 // whole workgroup) when L is past the end of the list.  With `xcd`, L follows
 // the XCD-aware order: workgroup b runs on XCD b % 8, so XCD x is given the
@@ -165,13 +181,6 @@ __device__ __forceinline__ bool find_work(const Tiles& tl, bool xcd, Work& out, 
 // software-pipelined in registers.
 // ---------------------------------------------------------------------------
 constexpr int BK = 32;
-constexpr int LDS_STAGE_MAX = (128 + 512) * BK * 2;  // bytes, largest tile pair
-
-__shared__ __attribute__((aligned(1024))) char ring0[LDS_STAGE_MAX];
-__shared__ __attribute__((aligned(1024))) char ring1[LDS_STAGE_MAX];
-__shared__ __attribute__((aligned(1024))) char ring2[LDS_STAGE_MAX];
-__shared__ __attribute__((aligned(1024))) char ring3[LDS_STAGE_MAX];
-
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 // SiLU(g) * u with the hardware exp2 and reciprocal (about 1 ulp each; the
@@ -262,11 +271,16 @@ __device__ __forceinline__ void store_tile(const f32x16 (&acc)[MI][NI], char* re
 //         fragments hold the same (row, column) in the same registers.
 // MODE 1: A = h [rows, m], W = w_down [E, d, m], C = y_perm [rows, d];
 //         B rows nt*BN.., C gets BN columns; wavefront w owns [w BN/4, ..).
+// workgroups per compute unit: two where two rings of four stages fit the LDS
+// (64 x 256 tiles), else one
+constexpr int rm_wgs(int BM, int BN) { return 2 * 4 * (BM + BN) * BK * 2 <= 160 * 1024 ? 2 : 1; }
+
 template <int MODE, int BM, int BN>
-__global__ __launch_bounds__(NTHR, 1) void ffn_gemm_bf16_kernel(
+__global__ __launch_bounds__(NTHR, rm_wgs(BM, BN)) void ffn_gemm_bf16_kernel(
     const uint16_t* __restrict__ A, const uint16_t* __restrict__ W, uint16_t* __restrict__ C,
-    const Tiles tl, int d, int m, const Guard g) {
+    const Tiles tl, int d, int m, const Header hd, const Guard g) {
   if (guard_skip(g)) return;
+  write_header(hd);
   constexpr int MI = BM / 32;             // 32-row fragments per wave (all tile rows)
   constexpr int NI = BN / 128;            // 32-col fragments per wave
   constexpr int AG = BM / 16;             // 1 KB DMA groups (16 rows) of the A tile
@@ -274,7 +288,11 @@ __global__ __launch_bounds__(NTHR, 1) void ffn_gemm_bf16_kernel(
   constexpr int GPW = (AG + BG) / 4;      // DMA instructions per wave per stage
   static_assert(AG % 4 == 0 && BG % 8 == 0, "groups split over 4 waves");
   static_assert(MODE == 1 || NI % 2 == 0, "gate/up fragments come in pairs");
-  static_assert((BM + BN) * BK * 2 <= LDS_STAGE_MAX, "stage too large");
+  constexpr int STAGE = (BM + BN) * BK * 2;  // bytes
+  __shared__ __attribute__((aligned(1024))) char ring0[STAGE];
+  __shared__ __attribute__((aligned(1024))) char ring1[STAGE];
+  __shared__ __attribute__((aligned(1024))) char ring2[STAGE];
+  __shared__ __attribute__((aligned(1024))) char ring3[STAGE];
 
   Work wk;
   if (!find_work(tl, true, wk, ring3)) return;
@@ -428,7 +446,7 @@ __global__ __launch_bounds__(NTHR, 1) void ffn_gemm_bf16_kernel(
   // ---- epilogue, staged through this wavefront's part of ring0
   __syncthreads();  // every wave is done with the ring
   constexpr int RS_MAX = (BN / 4) * 2 + 16;
-  static_assert(4 * 32 * RS_MAX <= LDS_STAGE_MAX, "epilogue staging fits in one ring stage");
+  static_assert(4 * 32 * RS_MAX <= STAGE, "epilogue staging fits in one ring stage");
   const int colbase = MODE == 0 ? nt * (BN / 2) + wv * (BN / 8) : nt * BN + wv * (BN / 4);
   store_tile<MODE, MI, NI>(acc, ring0 + wv * 32 * RS_MAX, C, ldc, wk, colbase, lane);
 }
@@ -809,10 +827,7 @@ __global__ __launch_bounds__(NTHR, 2) void ffn_gemm_packed_kernel(
 // than the item's transfers, so the first counted wait of the pipeline waits
 // for it too.)
 // ---------------------------------------------------------------------------
-constexpr int FFN_MAXE = 1024;
 constexpr int FFN_SPIN_LIMIT = 1 << 22;
-constexpr int FFN_CTR_TILES = 128;  // ctr index of done[0]
-constexpr int FFN_CTR_PATH = 5;     // in XCD 0's block, written only by clear_kernel
 
 struct XcdRange {
   int a0, a1;  // tiles [a0, a1) of this XCD
@@ -1551,8 +1566,9 @@ __device__ __forceinline__ void skinny_item(const uint16_t* __restrict__ A, cons
 template <int MODE, bool ROWMAJOR>
 __global__ __launch_bounds__(NTHR, 2) void ffn_gemm_skinny_kernel(
     const uint16_t* __restrict__ A, const uint16_t* __restrict__ W, uint16_t* __restrict__ C, const Tiles tl,
-    int d, int m, const RowGather gather, const Guard g) {
+    int d, int m, const RowGather gather, const Header hd, const Guard g) {
   if (guard_skip(g)) return;
+  write_header(hd);
   __shared__ __attribute__((aligned(1024))) char lds[SK_LDS];
   Work wk;
   if (!find_work(tl, true, wk, lds)) return;
@@ -1682,8 +1698,10 @@ template <int MODE, bool VEC>
 __global__ __launch_bounds__(256) void ffn_gemm_f32_kernel(const float* __restrict__ A,
                                                            const float* __restrict__ W,
                                                            float* __restrict__ C,
-                                                           const Tiles tl, int d, int m, const Guard g) {
+                                                           const Tiles tl, int d, int m, const Header hd,
+                                                           const Guard g) {
   if (guard_skip(g)) return;
+  write_header(hd);
   __shared__ f32x4 part[4][8][64];  // [wave][row block i, column block b][lane]
   __shared__ __attribute__((aligned(16))) char wl[64];
   Work wk;
@@ -1817,14 +1835,20 @@ int max_tiles_for(int rows_max, int E, int bm) { return (rows_max + bm - 1) / bm
 // by a few percent, depending on the routing).  Row-major weights: from 160.
 int pick_bm(int rows_max, int E, bool packed) { return rows_max >= (packed ? 48 : 160) * E ? 128 : 64; }
 
-// n-tiles per GEMM.  bf16 weight-row tile: 512 when it divides the expert's
-// rows (gate/up: 2m, down: d), else 256 -- `wide` selects 512; the packed
-// kernel always runs 256-row tiles at two workgroups per CU.  float32: 32
-// columns of h, 64 output columns.
-void n_tiles_of(bool bf16, bool packed, int d, int m, int& nn0, int& nn1, bool& wide0, bool& wide1) {
+// n-tiles per GEMM.  Row-major bf16 weights: 256-row weight tiles, and 512 at
+// 128-row token tiles where 512 divides the expert's rows (gate/up: 2m, down:
+// d) and half the compute units get a whole tile each (64-row token tiles run
+// two workgroups per compute unit at 256: both GEMMs of d 1024, m 640, 64
+// experts, top-6, 128 tokens 54.3 -> 46.5 us, 1200 tokens 102 -> 92, 777
+// tokens 70.2 -> 71.7; d 512, m 384, 48 experts, top-4, 2048 tokens, 128-row
+// token tiles 35.3 -> 28.4).  The packed kernel's two-launch form always
+// takes 256.  float32: 32 columns of h, 64 output columns.
+void n_tiles_of(bool bf16, bool packed, int rows_max, int bm, int d, int m, int& nn0, int& nn1, bool& wide0,
+                bool& wide1) {
   if (bf16) {
-    wide0 = !packed && (2 * m) % 512 == 0;
-    wide1 = !packed && d % 512 == 0;
+    const int tiles = rows_max / bm;
+    wide0 = !packed && bm == 128 && (2 * m) % 512 == 0 && tiles * (2 * m / 512) >= 128;
+    wide1 = !packed && bm == 128 && d % 512 == 0 && tiles * (d / 512) >= 128;
     nn0 = 2 * m / (wide0 ? 512 : 256);
     nn1 = d / (wide1 ? 512 : 256);
   } else {
@@ -1845,20 +1869,20 @@ bool use_skinny(int bm, int rows_max, int E) { return bm == kern::SK_BM && 2 * r
 // kernels are instantiated here, outside any function template (device stubs
 // of kernels first instantiated inside a template launcher are not emitted)
 #define FFN_GEMM(MODE, BM, BN)                                                   \
-  ffn_gemm_bf16_kernel<MODE, BM, BN><<<grid, NTHR, 0, s>>>(A, W, C, tl, d, m, g)
+  ffn_gemm_bf16_kernel<MODE, BM, BN><<<grid, NTHR, 0, s>>>(A, W, C, tl, d, m, hd, g)
 
 // row-major bf16 weights: one launch per GEMM
 hipError_t launch_gemm(int mode, int bm, bool wide, const Tiles& tl, const uint16_t* A,
-                       const uint16_t* W, uint16_t* C, int d, int m, hipStream_t s, Guard g) {
+                       const uint16_t* W, uint16_t* C, int d, int m, hipStream_t s, const kern::Header hd, Guard g) {
   if (use_skinny(bm, tl.rows_max, tl.E)) {
     Tiles ts = tl;
     ts.nn = mode == 0 ? m / 32 : d / 64;
     const int grid = (ts.max_tiles * ts.nn + 7) & ~7;
     const RowGather none{nullptr, 1, 0};
     if (mode == 0)
-      ffn_gemm_skinny_kernel<0, true><<<grid, NTHR, 0, s>>>(A, W, C, ts, d, m, none, g);
+      ffn_gemm_skinny_kernel<0, true><<<grid, NTHR, 0, s>>>(A, W, C, ts, d, m, none, hd, g);
     else
-      ffn_gemm_skinny_kernel<1, true><<<grid, NTHR, 0, s>>>(A, W, C, ts, d, m, none, g);
+      ffn_gemm_skinny_kernel<1, true><<<grid, NTHR, 0, s>>>(A, W, C, ts, d, m, none, hd, g);
     return hipGetLastError();
   }
   const int grid = (tl.max_tiles * tl.nn + 7) & ~7;  // whole XCD rounds
@@ -1866,13 +1890,13 @@ hipError_t launch_gemm(int mode, int bm, bool wide, const Tiles& tl, const uint1
     if (bm == 128) {
       if (wide) FFN_GEMM(0, 128, 512); else FFN_GEMM(0, 128, 256);
     } else {
-      if (wide) FFN_GEMM(0, 64, 512); else FFN_GEMM(0, 64, 256);
+      FFN_GEMM(0, 64, 256);
     }
   } else {
     if (bm == 128) {
       if (wide) FFN_GEMM(1, 128, 512); else FFN_GEMM(1, 128, 256);
     } else {
-      if (wide) FFN_GEMM(1, 64, 512); else FFN_GEMM(1, 64, 256);
+      FFN_GEMM(1, 64, 256);
     }
   }
   return hipGetLastError();
@@ -1969,7 +1993,7 @@ hipError_t launch_packed(int bm, const Tiles& t0, int nn1, const uint16_t* X, co
     if (skinny) {
       Tiles ts = t0;
       ts.nn = m / 32;
-      ffn_gemm_skinny_kernel<0, false><<<(ts.max_tiles * ts.nn + 7) & ~7, NTHR, 0, s>>>(A, W, C, ts, d, m, rg, g);
+      ffn_gemm_skinny_kernel<0, false><<<(ts.max_tiles * ts.nn + 7) & ~7, NTHR, 0, s>>>(A, W, C, ts, d, m, rg, kern::Header{nullptr, 0}, g);
     } else if (bm == 128)
       FFN_PACKED(0, 128);
     else
@@ -1986,7 +2010,8 @@ hipError_t launch_packed(int bm, const Tiles& t0, int nn1, const uint16_t* X, co
     const RowGather rg{nullptr, 1, 0};
     if (skinny) {
       t.nn = d / 64;
-      ffn_gemm_skinny_kernel<1, false><<<(t.max_tiles * t.nn + 7) & ~7, NTHR, 0, s>>>(A, W, C, t, d, m, rg, g);
+      ffn_gemm_skinny_kernel<1, false><<<(t.max_tiles * t.nn + 7) & ~7, NTHR, 0, s>>>(A, W, C, t, d, m, rg,
+                                                                                      kern::Header{nullptr, 0}, g);
     } else if (bm == 128)
       FFN_PACKED(1, 128);
     else
@@ -2040,7 +2065,7 @@ hipError_t launch_expert_ffn(const void* x_perm, bool bf16, const int32_t* offse
   const int bm = bf16 ? pick_bm(rows_max, E, packed) : FBM;
   int nn0, nn1;
   bool wide0, wide1;
-  n_tiles_of(bf16, packed, d, m, nn0, nn1, wide0, wide1);
+  n_tiles_of(bf16, packed, rows_max, bm, d, m, nn0, nn1, wide0, wide1);
   Tiles t0{offsets, K_dev, E, K_dev ? n_K : 0, rows_max, bm, max_tiles_for(rows_max, E, bm), nn0,
            kmin};
   Tiles t1 = t0;
@@ -2054,14 +2079,13 @@ hipError_t launch_expert_ffn(const void* x_perm, bool bf16, const int32_t* offse
                         static_cast<uint16_t*>(h), static_cast<uint16_t*>(y_perm), d, m, gather, ctr, s, g,
                         counters_ready);
   }
-  err = clear_counters(ctr, 0, bf16 ? FFN_PATH_ROW_MAJOR : FFN_PATH_F32, s, g);
-  if (err != hipSuccess) return err;
+  const kern::Header hd{ctr, bf16 ? FFN_PATH_ROW_MAJOR : FFN_PATH_F32}, none{nullptr, 0};
   if (bf16) {
     err = launch_gemm(0, bm, wide0, t0, static_cast<const uint16_t*>(x_perm),
-                      static_cast<const uint16_t*>(w_gate_up), static_cast<uint16_t*>(h), d, m, s, g);
+                      static_cast<const uint16_t*>(w_gate_up), static_cast<uint16_t*>(h), d, m, s, hd, g);
     if (err != hipSuccess) return err;
     return launch_gemm(1, bm, wide1, t1, static_cast<const uint16_t*>(h),
-                       static_cast<const uint16_t*>(w_down), static_cast<uint16_t*>(y_perm), d, m, s, g);
+                       static_cast<const uint16_t*>(w_down), static_cast<uint16_t*>(y_perm), d, m, s, none, g);
   }
   const bool vec = d % 4 == 0 && m % 4 == 0;  // 16-byte rows (the arrays themselves are 16-byte aligned)
   const int g0 = t0.max_tiles * nn0, g1 = t1.max_tiles * nn1;
@@ -2069,15 +2093,15 @@ hipError_t launch_expert_ffn(const void* x_perm, bool bf16, const int32_t* offse
        df = static_cast<const float*>(w_down);
   auto hf = static_cast<float*>(h), yf = static_cast<float*>(y_perm);
   if (vec)
-    ffn_gemm_f32_kernel<0, true><<<g0, NTHR, 0, s>>>(xf, wf, hf, t0, d, m, g);
+    ffn_gemm_f32_kernel<0, true><<<g0, NTHR, 0, s>>>(xf, wf, hf, t0, d, m, hd, g);
   else
-    ffn_gemm_f32_kernel<0, false><<<g0, NTHR, 0, s>>>(xf, wf, hf, t0, d, m, g);
+    ffn_gemm_f32_kernel<0, false><<<g0, NTHR, 0, s>>>(xf, wf, hf, t0, d, m, hd, g);
   err = hipGetLastError();
   if (err != hipSuccess) return err;
   if (vec)
-    ffn_gemm_f32_kernel<1, true><<<g1, NTHR, 0, s>>>(hf, df, yf, t1, d, m, g);
+    ffn_gemm_f32_kernel<1, true><<<g1, NTHR, 0, s>>>(hf, df, yf, t1, d, m, none, g);
   else
-    ffn_gemm_f32_kernel<1, false><<<g1, NTHR, 0, s>>>(hf, df, yf, t1, d, m, g);
+    ffn_gemm_f32_kernel<1, false><<<g1, NTHR, 0, s>>>(hf, df, yf, t1, d, m, none, g);
   return hipGetLastError();
 }
 
