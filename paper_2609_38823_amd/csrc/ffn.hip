@@ -812,7 +812,8 @@ __global__ __launch_bounds__(NTHR, 2) void ffn_gemm_packed_kernel(
 //   ctr[16 x]      claim counter of XCD x (the 64 bytes from 16 x are written
 //   ctr[16 x + 1]  items completed on XCD x       only by workgroups of XCD x)
 //   ctr[16 x + 2]  waits on XCD x that ran out of polls
-//   ctr[16 x + 3]  items in the whole plan (every workgroup of XCD x stores it)
+//   ctr[16 x + 3]  items in the whole plan (stored by workgroup 0 only: stores of
+//                  all workgroups to one address are served one by one)
 //   ctr[FFN_CTR_PATH]  launch path of the call (FFN_PATH_*; set by clear_kernel)
 //   ctr[128 + t]   gate/up items of m-tile t completed
 // ctr (128 + max_tiles ints) is zeroed by clear_kernel before each launch.
@@ -1031,10 +1032,9 @@ __global__ __launch_bounds__(NTHR, 2) void ffn_fused_kernel(
   const int n_gu = ntile * tl.nn, n_all = n_gu + ntile * nn1;
   const int tid = threadIdx.x;
   int* const claim = ctr + 16 * xcc;
-  if (tid == 0)  // every workgroup of this XCD stores the same value
-    __hip_atomic_store(claim + 3, s_tstart[tl.E] * (tl.nn + nn1), __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
-  for (;;) {
+  if (blockIdx.x == 0 && tid == 0) claim[3] = s_tstart[tl.E] * (tl.nn + nn1);
+  int n_done = 0;  // counted at the end: an atomic per item would stand before the next item's loads
+  for (;; ++n_done) {
     __syncthreads();  // the previous item is done with LDS and s_item
     if (tid == 0) s_item = atomicAdd(claim, 1);
     __syncthreads();
@@ -1056,8 +1056,8 @@ __global__ __launch_bounds__(NTHR, 2) void ffn_fused_kernel(
       else if constexpr (AUX != 2)
         packed_item<1, BM, BN1, AUX>(H, Wdn, Y, it.wk, d, m, RowGather{nullptr, 1, 0}, aring);
     }
-    if (tid == 0) __hip_atomic_fetch_add(claim + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
+  if (tid == 0 && n_done) __hip_atomic_fetch_add(claim + 1, n_done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // ---------------------------------------------------------------------------
@@ -1284,9 +1284,9 @@ __global__ __launch_bounds__(PP_THR, 1) void ffn_pingpong_kernel(
   const int ntile = rg.a1 - rg.a0;
   const int n_gu = ntile * tl.nn, n_all = n_gu + ntile * nn1;
   int* const claim = ctr + 16 * xcc;
-  if (tid == 0)
-    __hip_atomic_store(claim + 3, s_tstart[tl.E] * (tl.nn + nn1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  for (;;) {
+  if (blockIdx.x == 0 && tid == 0) claim[3] = s_tstart[tl.E] * (tl.nn + nn1);
+  int n_done = 0;
+  for (;; ++n_done) {
     __syncthreads();  // the previous item is done with LDS and s_item
     if (tid == 0) s_item = atomicAdd(claim, 1);
     __syncthreads();
@@ -1307,8 +1307,8 @@ __global__ __launch_bounds__(PP_THR, 1) void ffn_pingpong_kernel(
       else
         pingpong_item<1, 0>(H, Wdn, Y, it.wk, d, m, RowGather{nullptr, 1, 0}, st0, st1, st2, st3, grp);
     }
-    if (tid == 0) __hip_atomic_fetch_add(claim + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
+  if (tid == 0 && n_done) __hip_atomic_fetch_add(claim + 1, n_done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // ---------------------------------------------------------------------------
