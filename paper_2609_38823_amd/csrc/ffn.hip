@@ -524,6 +524,19 @@ __device__ __forceinline__ u32x4 load_frag(__amdgpu_buffer_rsrc_t rs, int voff, 
   return __builtin_amdgcn_raw_buffer_load_b128(rs, voff, soff, AUX);
 }
 
+// Thread 0's claim of the workgroup's next item, issued before the plan or once
+// an item's last loads are consumed, so that its latency runs under the plan or
+// the epilogue (128 x 512 tiles: 4096 dense rows 418 -> 415 us a layer; older
+// than an item's transfers it would delay them).  64-row tiles, which stream
+// weights, claim as late as they can: their queues end more evenly (23 tokens
+// 540 us a pass, claiming ahead 551).
+// The per-lane address keeps the compiler from broadcasting the result, and
+// so from waiting for it, here.
+__device__ __forceinline__ int claim_ahead(int* claim) {
+  asm volatile("" : "+v"(claim));
+  return threadIdx.x == 0 ? atomicAdd(claim, 1) : 0;
+}
+
 // One work item: the BM x BN output tile `wk` of one GEMM.  `aring` is the
 // workgroup's LDS: four A stages of a_slot<BM, BN>() bytes.  The caller
 // synchronises the workgroup before the item reuses it.
@@ -823,10 +836,7 @@ __global__ __launch_bounds__(NTHR, 2) void ffn_gemm_packed_kernel(
 // Cost of a tile: 4 + its active 32-row blocks; the first tile of an expert
 // costs more for the weight fetch that its later m-tiles find in L2: 2 with
 // 128-row tiles, a whole tile's cost with 64-row tiles (few rows per
-// expert, where an XCD's time follows the weight bytes it streams).  (Claiming
-// the next item while the current one runs does not pay: the claim is older
-// than the item's transfers, so the first counted wait of the pipeline waits
-// for it too.)
+// expert, where an XCD's time follows the weight bytes it streams).
 // ---------------------------------------------------------------------------
 constexpr int FFN_SPIN_LIMIT = 1 << 22;
 
@@ -1027,11 +1037,11 @@ __global__ __launch_bounds__(NTHR, 2) void ffn_fused_kernel(
 
   // the XCD this workgroup runs on (hardware register XCC_ID, bits 3:0)
   const int xcc = (int)(__builtin_amdgcn_s_getreg((3 << 11) | 20) % (unsigned)n_xcc);
+  const int tid = threadIdx.x;
+  int* const claim = ctr + 16 * xcc;
   const XcdRange rg = plan_tiles<NTHR>(tl, xcc, n_xcc, s_tstart, s_part);
   const int ntile = rg.a1 - rg.a0;
   const int n_gu = ntile * tl.nn, n_all = n_gu + ntile * nn1;
-  const int tid = threadIdx.x;
-  int* const claim = ctr + 16 * xcc;
   if (blockIdx.x == 0 && tid == 0) claim[3] = s_tstart[tl.E] * (tl.nn + nn1);
   int n_done = 0;  // counted at the end: an atomic per item would stand before the next item's loads
   for (;; ++n_done) {
@@ -1089,7 +1099,7 @@ template <int MODE, int AUX>
 __device__ __forceinline__ void pingpong_item(const uint16_t* __restrict__ A, const uint16_t* __restrict__ Wp,
                                               uint16_t* __restrict__ C, const Work wk, int d, int m,
                                               const RowGather gather, char* st0, char* st1, char* st2,
-                                              char* st3, int grp) {
+                                              char* st3, int grp, int* claim, int* s_next) {
   constexpr int MI = 4, NI = 2, AGW = 2, LA = 3;
   const int nt = wk.nt;
   const int Kdim = MODE == 0 ? d : m;
@@ -1247,11 +1257,13 @@ __device__ __forceinline__ void pingpong_item(const uint16_t* __restrict__ A, co
   else
     pipeline(std::integral_constant<int, 1>{});
 
+  const int next = claim_ahead(claim);
   // epilogue: every wavefront has passed the last barrier after its last LDS
   // read; wavefront w stages its slice through half w / 4 of stage slot w % 4
   char* reg = ((wv & 3) == 0 ? st0 : (wv & 3) == 1 ? st1 : (wv & 3) == 2 ? st2 : st3) + (wv >> 2) * (PP_SLOT / 2);
   const int colbase = MODE == 0 ? nt * 256 + 32 * wv : nt * 512 + 64 * wv;
   store_tile<MODE, MI, NI>(acc, reg, C, ldc, wk, colbase, lane);
+  if (threadIdx.x == 0) *s_next = next;
 }
 
 // The persistent loop of ffn_fused_kernel with 128 x 512 tiles on
@@ -1275,6 +1287,8 @@ __global__ __launch_bounds__(PP_THR, 1) void ffn_pingpong_kernel(
   // the SIMD of each wavefront (hardware register HW_ID, bits 5:4)
   if ((tid & 63) == 0) s_simd[tid >> 6] = (int)(__builtin_amdgcn_s_getreg((1 << 11) | (4 << 6) | 4) & 3);
   const int xcc = (int)(__builtin_amdgcn_s_getreg((3 << 11) | 20) % (unsigned)n_xcc);
+  int* const claim = ctr + 16 * xcc;
+  const int first = claim_ahead(claim);  // its latency runs under the plan's
   const XcdRange rg = plan_tiles<PP_THR>(tl, xcc, n_xcc, s_tstart, s_part);  // its barriers publish s_simd
   // group 1: a lower-numbered wavefront shares this one's SIMD (the barrier
   // counts of pingpong_item do not depend on the groups)
@@ -1283,29 +1297,27 @@ __global__ __launch_bounds__(PP_THR, 1) void ffn_pingpong_kernel(
   grp = __builtin_amdgcn_readfirstlane(grp);
   const int ntile = rg.a1 - rg.a0;
   const int n_gu = ntile * tl.nn, n_all = n_gu + ntile * nn1;
-  int* const claim = ctr + 16 * xcc;
+  if (tid == 0) s_item = first;
   if (blockIdx.x == 0 && tid == 0) claim[3] = s_tstart[tl.E] * (tl.nn + nn1);
   int n_done = 0;
   for (;; ++n_done) {
-    __syncthreads();  // the previous item is done with LDS and s_item
-    if (tid == 0) s_item = atomicAdd(claim, 1);
-    __syncthreads();
+    __syncthreads();  // the previous item is done with LDS; s_item is the next one
     const int j = __builtin_amdgcn_readfirstlane(s_item);
     if (j >= n_all) break;
     const Item it = decode_item(tl, rg, s_tstart, j, n_gu, nn1, BM);
     int* const done = ctr + FFN_CTR_TILES + it.t;
     if (!it.down) {
       if (it.stream)
-        pingpong_item<0, 2>(X, Wgu, H, it.wk, d, m, gather, st0, st1, st2, st3, grp);
+        pingpong_item<0, 2>(X, Wgu, H, it.wk, d, m, gather, st0, st1, st2, st3, grp, claim, &s_item);
       else
-        pingpong_item<0, 0>(X, Wgu, H, it.wk, d, m, gather, st0, st1, st2, st3, grp);
+        pingpong_item<0, 0>(X, Wgu, H, it.wk, d, m, gather, st0, st1, st2, st3, grp, claim, &s_item);
       gate_up_done(done);
     } else {
       wait_gate_up(done, tl.nn, claim + 2);
       if (it.stream)
-        pingpong_item<1, 2>(H, Wdn, Y, it.wk, d, m, RowGather{nullptr, 1, 0}, st0, st1, st2, st3, grp);
+        pingpong_item<1, 2>(H, Wdn, Y, it.wk, d, m, RowGather{nullptr, 1, 0}, st0, st1, st2, st3, grp, claim, &s_item);
       else
-        pingpong_item<1, 0>(H, Wdn, Y, it.wk, d, m, RowGather{nullptr, 1, 0}, st0, st1, st2, st3, grp);
+        pingpong_item<1, 0>(H, Wdn, Y, it.wk, d, m, RowGather{nullptr, 1, 0}, st0, st1, st2, st3, grp, claim, &s_item);
     }
   }
   if (tid == 0 && n_done) __hip_atomic_fetch_add(claim + 1, n_done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

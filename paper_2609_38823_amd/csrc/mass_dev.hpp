@@ -82,7 +82,7 @@ __device__ __forceinline__ double mass_of_entries(const int (&key)[R], const flo
 
 // the same for the n_all routing entries from idx + base (token-major), each
 // wavefront loading its own slice into registers
-__device__ double mass_sorted(const int32_t* __restrict__ idx, const float* __restrict__ w, size_t base,
+__device__ __forceinline__ double mass_sorted(const int32_t* __restrict__ idx, const float* __restrict__ w, size_t base,
                               int n_all, int E, int key_bits, CalLds& L) {
   const int lane = threadIdx.x & 63;
   const int nr = slice_rounds(n_all), lo = slice_lo(n_all, nr), hi = min(n_all, lo + nr * kWave);

@@ -149,7 +149,7 @@ __device__ __forceinline__ void sort_rounds(const int32_t* keys, int A, int E, i
   });
 }
 // wh: DS_WAVES rows of E ints
-__device__ void sort_small(const int32_t* keys, int A, int E, int key_bits, int* wh, int* part,
+__device__ __forceinline__ void sort_small(const int32_t* keys, int A, int E, int key_bits, int* wh, int* part,
                            int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
                            int32_t* __restrict__ src_of_row, int32_t* __restrict__ row_of_slot) {
   with_rounds(slice_rounds(A), [&](auto RC) {
