@@ -524,19 +524,6 @@ __device__ __forceinline__ u32x4 load_frag(__amdgpu_buffer_rsrc_t rs, int voff, 
   return __builtin_amdgcn_raw_buffer_load_b128(rs, voff, soff, AUX);
 }
 
-// Thread 0's claim of the workgroup's next item, issued before the plan or once
-// an item's last loads are consumed, so that its latency runs under the plan or
-// the epilogue (128 x 512 tiles: 4096 dense rows 418 -> 415 us a layer; older
-// than an item's transfers it would delay them).  64-row tiles, which stream
-// weights, claim as late as they can: their queues end more evenly (23 tokens
-// 540 us a pass, claiming ahead 551).
-// The per-lane address keeps the compiler from broadcasting the result, and
-// so from waiting for it, here.
-__device__ __forceinline__ int claim_ahead(int* claim) {
-  asm volatile("" : "+v"(claim));
-  return threadIdx.x == 0 ? atomicAdd(claim, 1) : 0;
-}
-
 // One work item: the BM x BN output tile `wk` of one GEMM.  `aring` is the
 // workgroup's LDS: four A stages of a_slot<BM, BN>() bytes.  The caller
 // synchronises the workgroup before the item reuses it.
@@ -827,9 +814,11 @@ __global__ __launch_bounds__(NTHR, 2) void ffn_gemm_packed_kernel(
 //   ctr[16 x + 2]  waits on XCD x that ran out of polls
 //   ctr[16 x + 3]  items in the whole plan (stored by workgroup 0 only: stores of
 //                  all workgroups to one address are served one by one)
-//   ctr[FFN_CTR_PATH]  launch path of the call (FFN_PATH_*; set by clear_kernel)
+//   ctr[FFN_CTR_PATH]  launch path of the call (FFN_PATH_*)
 //   ctr[128 + t]   gate/up items of m-tile t completed
-// ctr (128 + max_tiles ints) is zeroed by clear_kernel before each launch.
+// ctr (128 + max_tiles ints) is zeroed, and the path set, before each launch: by
+// clear_kernel, or by the routing launch of the one-call layers.  Kernels that
+// use no counters write the 128 header ints themselves (write_header).
 // A call ran every item of its plan exactly when no wait ran out and the
 // completed counts add up to the plan: an XCD that received no workgroup
 // leaves its items unclaimed and the sum short.
@@ -1099,7 +1088,7 @@ template <int MODE, int AUX>
 __device__ __forceinline__ void pingpong_item(const uint16_t* __restrict__ A, const uint16_t* __restrict__ Wp,
                                               uint16_t* __restrict__ C, const Work wk, int d, int m,
                                               const RowGather gather, char* st0, char* st1, char* st2,
-                                              char* st3, int grp, int* claim, int* s_next) {
+                                              char* st3, int grp) {
   constexpr int MI = 4, NI = 2, AGW = 2, LA = 3;
   const int nt = wk.nt;
   const int Kdim = MODE == 0 ? d : m;
@@ -1257,13 +1246,11 @@ __device__ __forceinline__ void pingpong_item(const uint16_t* __restrict__ A, co
   else
     pipeline(std::integral_constant<int, 1>{});
 
-  const int next = claim_ahead(claim);
   // epilogue: every wavefront has passed the last barrier after its last LDS
   // read; wavefront w stages its slice through half w / 4 of stage slot w % 4
   char* reg = ((wv & 3) == 0 ? st0 : (wv & 3) == 1 ? st1 : (wv & 3) == 2 ? st2 : st3) + (wv >> 2) * (PP_SLOT / 2);
   const int colbase = MODE == 0 ? nt * 256 + 32 * wv : nt * 512 + 64 * wv;
   store_tile<MODE, MI, NI>(acc, reg, C, ldc, wk, colbase, lane);
-  if (threadIdx.x == 0) *s_next = next;
 }
 
 // The persistent loop of ffn_fused_kernel with 128 x 512 tiles on
@@ -1288,7 +1275,6 @@ __global__ __launch_bounds__(PP_THR, 1) void ffn_pingpong_kernel(
   if ((tid & 63) == 0) s_simd[tid >> 6] = (int)(__builtin_amdgcn_s_getreg((1 << 11) | (4 << 6) | 4) & 3);
   const int xcc = (int)(__builtin_amdgcn_s_getreg((3 << 11) | 20) % (unsigned)n_xcc);
   int* const claim = ctr + 16 * xcc;
-  const int first = claim_ahead(claim);  // its latency runs under the plan's
   const XcdRange rg = plan_tiles<PP_THR>(tl, xcc, n_xcc, s_tstart, s_part);  // its barriers publish s_simd
   // group 1: a lower-numbered wavefront shares this one's SIMD (the barrier
   // counts of pingpong_item do not depend on the groups)
@@ -1297,27 +1283,28 @@ __global__ __launch_bounds__(PP_THR, 1) void ffn_pingpong_kernel(
   grp = __builtin_amdgcn_readfirstlane(grp);
   const int ntile = rg.a1 - rg.a0;
   const int n_gu = ntile * tl.nn, n_all = n_gu + ntile * nn1;
-  if (tid == 0) s_item = first;
   if (blockIdx.x == 0 && tid == 0) claim[3] = s_tstart[tl.E] * (tl.nn + nn1);
   int n_done = 0;
   for (;; ++n_done) {
-    __syncthreads();  // the previous item is done with LDS; s_item is the next one
+    __syncthreads();  // the previous item is done with LDS and s_item
+    if (tid == 0) s_item = atomicAdd(claim, 1);
+    __syncthreads();
     const int j = __builtin_amdgcn_readfirstlane(s_item);
     if (j >= n_all) break;
     const Item it = decode_item(tl, rg, s_tstart, j, n_gu, nn1, BM);
     int* const done = ctr + FFN_CTR_TILES + it.t;
     if (!it.down) {
       if (it.stream)
-        pingpong_item<0, 2>(X, Wgu, H, it.wk, d, m, gather, st0, st1, st2, st3, grp, claim, &s_item);
+        pingpong_item<0, 2>(X, Wgu, H, it.wk, d, m, gather, st0, st1, st2, st3, grp);
       else
-        pingpong_item<0, 0>(X, Wgu, H, it.wk, d, m, gather, st0, st1, st2, st3, grp, claim, &s_item);
+        pingpong_item<0, 0>(X, Wgu, H, it.wk, d, m, gather, st0, st1, st2, st3, grp);
       gate_up_done(done);
     } else {
       wait_gate_up(done, tl.nn, claim + 2);
       if (it.stream)
-        pingpong_item<1, 2>(H, Wdn, Y, it.wk, d, m, RowGather{nullptr, 1, 0}, st0, st1, st2, st3, grp, claim, &s_item);
+        pingpong_item<1, 2>(H, Wdn, Y, it.wk, d, m, RowGather{nullptr, 1, 0}, st0, st1, st2, st3, grp);
       else
-        pingpong_item<1, 0>(H, Wdn, Y, it.wk, d, m, RowGather{nullptr, 1, 0}, st0, st1, st2, st3, grp, claim, &s_item);
+        pingpong_item<1, 0>(H, Wdn, Y, it.wk, d, m, RowGather{nullptr, 1, 0}, st0, st1, st2, st3, grp);
     }
   }
   if (tid == 0 && n_done) __hip_atomic_fetch_add(claim + 1, n_done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1344,6 +1331,13 @@ __global__ __launch_bounds__(PP_THR, 1) void ffn_pingpong_kernel(
 // agent scope (sc1: written through, and read past, the XCD's own L2).  A
 // down item issues its first weights before it waits for its tile's gate/up
 // items, which were all claimed before it by running workgroups.
+//
+// The first claim is issued before the plan and the next one under an item's
+// last products.  (In ffn_fused_kernel the claim stays after the plan and
+// between the items: it would be older than an item's direct-to-LDS transfers,
+// which are waited for by counting.  Here every load goes to registers, the
+// compiler places every wait, and both claims are consumed before the barrier
+// that publishes them.)
 // ---------------------------------------------------------------------------
 constexpr int SK_BM = 64;              // token rows per tile (one or two 32-row blocks)
 constexpr int AUX_NT = 2, AUX_SC1 = 16;  // non-temporal; agent scope
@@ -1437,9 +1431,12 @@ __device__ __forceinline__ void skinny_tile(const uint16_t* __restrict__ A, cons
   };
   int next = 0;
   auto claim_next = [&]() {
-    int* c = claim;
-    asm volatile("" : "+v"(c));  // a per-lane address: the result is not broadcast (and waited for) here
-    if (claim && tid == 0) next = atomicAdd(c, 1);
+    // a per-lane address, so that the result is not broadcast (and waited for)
+    // here, and a global one: a flat atomic would also count as an LDS
+    // operation, and no load could be waited for without waiting for it
+    auto c = reinterpret_cast<__attribute__((address_space(1))) int*>(reinterpret_cast<uintptr_t>(claim));
+    asm volatile("" : "+v"(c));
+    if (claim && tid == 0) next = __hip_atomic_fetch_add(c, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   };
 
   // k-block i sits in slot i % RING.  Packed weights: a slot is refilled with
