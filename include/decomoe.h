@@ -196,7 +196,7 @@ int moe_route_packed(const void* x, moe_dtype dtype, const void* w_r_packed, con
  *                     order[j] is the expert placed at position j.  With no
  *                     non-empty segment the order is the identity.
  * A token's experts are distinct in moe_route output.  An expert repeated
- * within a token: in segments of up to 16384 entries (with E <= 512) its
+ * within a token: in segments of up to 8192 entries (with E <= 512) its
  * weights are added one by one in slot order, like distinct experts; in
  * larger segments they are first summed within the token (in unspecified
  * order when it repeats three times or more).
@@ -229,9 +229,10 @@ int moe_calibrate_prefix(const int32_t* topk_idx, const float* topk_w,
  *                     their renormalised weights.
  * Bitwise the same results as moe_calibrate_prefix (one segment, order =
  * NULL) followed by moe_route on the logits with K_dev = K_out.  When
- * T*k <= 16384 and E <= 512 it runs as one launch in which every workgroup
- * forms the masses and K itself (a few thousand routing entries) before
- * re-routing its share of the tokens; otherwise as those two launches.
+ * E <= 512 and either T*k <= 8192 or T <= 256 floor(64 / k) with k <= 16 or
+ * E > 256 (k = 8: up to 2048 tokens), it runs as one launch in which every
+ * workgroup forms the masses and K itself before re-routing its share of the
+ * tokens; otherwise as those two launches.
  * Outputs must not overlap the inputs (MOE_EALIAS).  Limits: 1 <= k <=
  * min(E, 32), E <= 1024.  ws / ws_bytes: not needed (NULL, 0 accepted).
  */
@@ -248,10 +249,11 @@ int moe_calibrate_route_prefix(const float* logits, const int32_t* topk_idx_full
  *   moe_calibrate_route_prefix(p)                  -> mass, K_out, topk_idx, topk_w
  *   moe_dispatch(topk_idx, x = NULL)               -> counts, offsets, src_of_row, row_of_slot
  * with the same arguments, layouts, limits and errors (bf16 x, packed
- * router weights; 1 <= k <= min(E, 32); p in (0, 1]).  When T*k <= 16384
- * and E <= 512, the masses, K, the re-route and the grouping run as one
- * launch after the router's (the last of its workgroups to finish groups
- * the entries); otherwise the three calls run.  T = 0 gives K = k and empty
+ * router weights; 1 <= k <= min(E, 32); p in (0, 1]).  At the sizes that
+ * moe_calibrate_route_prefix runs as one launch, the masses, K, the re-route
+ * and the grouping run as one launch behind the router and the Top-k (the last
+ * of its workgroups to finish groups the entries), and up to 16 tokens (k <= 16,
+ * E <= 128) the Top-k too; otherwise the three calls run.  T = 0 gives K = k and empty
  * counts.  Needs ws (moe_workspace_size).
  */
 int moe_route_rcep(const void* x, moe_dtype dtype, const void* w_r_packed, const float* bias, int T, int d,
@@ -304,11 +306,11 @@ int moe_dense_layer(const void* x, moe_dtype dtype, const void* w_r_packed, cons
  * `out` [T, d] may be `residual`, `x`, or both (the hidden state updated in
  * place: the combine is the last launch); any other overlap of out with an
  * input, and any overlap among the other outputs and inputs, is MOE_EALIAS.
- * When the routing groups its entries in one launch (T*k <= 16384,
- * E <= 512) and the expert FFN runs persistent, that launch also clears the
- * expert FFN's work counters, so the layer is four launches (router,
- * Top-k, calibration with re-route and grouping, expert FFN) plus the
- * combine; moe_ffn_status afterwards reports the FFN as for
+ * When the routing groups its entries in one launch (moe_route_rcep) and the
+ * expert FFN runs persistent, that launch also clears the expert FFN's work
+ * counters, so the layer is four launches (router, Top-k, calibration with
+ * re-route and grouping, expert FFN; three where the Top-k runs in the
+ * calibration's launch) plus the combine; moe_ffn_status afterwards reports the FFN as for
  * moe_expert_ffn_packed_gather.  T = 0 gives K = k and empty counts and
  * launches nothing else.  ws needs max(moe_route_rcep's, the expert FFN's)
  * bytes (moe_workspace_size covers both).
@@ -348,11 +350,12 @@ int moe_rcep_layer(const void* x, moe_dtype dtype, const void* w_r_packed, const
  * the call writes them); any other overlap of an argument with an output
  * is MOE_EALIAS.  When the router's plan keeps a token tile of at most
  * 32 KB per workgroup (one expert group: E <= 128) and the routing groups
- * its entries in one launch (T*k <= 16384), the combine runs inside the
+ * its entries in one launch (moe_route_rcep), the combine runs inside the
  * router's launch: each router workgroup forms the rows and columns of h it
  * multiplies, writes them and keeps them in LDS; the layer is then four
  * launches (router with the previous combine, Top-k, calibration with
- * re-route and grouping, expert FFN).  Otherwise the combine is a launch of
+ * re-route and grouping, expert FFN; three where the Top-k runs in the
+ * calibration's launch).  Otherwise the combine is a launch of
  * its own.  Same limits, errors and workspace as moe_rcep_layer; T = 0
  * gives K = k and empty counts.
  */

@@ -25,9 +25,8 @@ __global__ __launch_bounds__(CAL_THREADS) void segment_mass_kernel(
     hi = clampi(seg_offsets[seg + 1], lo, T);
   }
   const int n_all = (hi - lo) * k;
-  const double a = n_all <= CAL_SORT_A && E <= CAL_SORT_E
-                       ? mass_sorted(idx, w, (size_t)lo * k, n_all, E, key_bits, L)
-                       : mass_chunked(idx, w, lo, hi, E, k, L);
+  const double a = cal_sorted(n_all, E, k) ? mass_sorted(idx, w, lo, n_all, E, k, key_bits, L)
+                                           : mass_chunked(idx, w, lo, hi, E, k, L);
   if (tid < E) mass[(size_t)seg * E + tid] = a;
   if (K_out) {
     const int K = prefix_K(E, k, p, L);

@@ -3,17 +3,19 @@
 // prefix re-route kernel.  Every function here is called by all
 // CAL_THREADS threads of the workgroup (they synchronise it).
 //
-//   mass_sorted   up to CAL_SORT_A routing entries and E <= CAL_SORT_E: the
-//                 entries are loaded into registers and their weights grouped
-//                 by expert with a stable counting sort in LDS (token order
-//                 kept within an expert); thread e adds its expert's weights
-//                 in that order
+//   mass_sorted   where cal_sorted() holds (up to CAL_SORT_A routing entries and
+//                 E <= CAL_SORT_E): the entries are loaded into registers and
+//                 their weights grouped by expert with a stable counting sort
+//                 in LDS (token order kept within an expert); thread e adds its
+//                 expert's weights in that order
 //   mass_chunked  larger invocations: chunks of tokens are scattered into a
 //                 dense LDS table [token][expert] (float64) and thread e
 //                 adds column e in ascending token order
 // Either way one float64 running sum per expert over the tokens: the
 // sequence of additions of the plain definition (unrouted tokens add zeros,
-// which change nothing).
+// which change nothing).  An expert repeated within a token: up to CAL_STAGE
+// entries its weights are added one by one, beyond they are summed within the
+// token first, on either path.
 //   prefix_K      the running sum c_K over the experts by one wavefront, then
 //                 the first K with c_K >= p * c_E by a ballot; K = max(k, K)
 #pragma once
@@ -32,6 +34,18 @@ constexpr int CAL_WAVES = CAL_THREADS / kWave;
 constexpr int CAL_SORT_A = DS_MAX;  // routing entries of the sorted path
 constexpr int CAL_SORT_E = 512;  // the sorted path keeps [waves][E] counts in the table
 
+// Whether n_all = tokens * k entries take the sorted path.  Beyond CAL_STAGE
+// entries its rounds hold whole tokens.  The dense table has one addition per
+// token where the sorted path has one per entry of an expert, so it stays ahead
+// where few tokens make many entries (calibration + re-route of 262 tokens, k 32:
+// E 32 24.7 us against 26.6, E 256 31.5 against 34.1, E 512 51.9 against 43.9;
+// 525 tokens, k 16: E 32 25.3 against 24.1, E 256 32.6 against 32.3).
+__host__ __device__ inline bool cal_sorted(size_t n_all, int E, int k) {
+  if (E > CAL_SORT_E) return false;
+  if (n_all <= (size_t)CAL_STAGE) return true;
+  return (k <= 16 || E > 256) && n_all <= (size_t)(CAL_SORT_A / kWave) * (kWave / k * k);
+}
+
 // Tokens per chunk: the table holds ch x E doubles and a chunk holds at most
 // CAL_ENT routing entries.
 __host__ __device__ inline int cal_chunk(int E, int k) {
@@ -40,7 +54,8 @@ __host__ __device__ inline int cal_chunk(int E, int k) {
   return c < 64 ? c : 64;
 }
 
-static_assert(CAL_THREADS == DS_THREADS && CAL_SORT_A <= 2 * CAL_STAGE && CAL_WAVES * CAL_SORT_E <= 2 * CAL_TABLE,
+static_assert(CAL_THREADS == DS_THREADS && CAL_SORT_A <= 2 * CAL_STAGE && CAL_WAVES * CAL_SORT_E <= 2 * CAL_TABLE &&
+                  CAL_STAGE == DS_MAX / 2,
               "the sorted path's arrays fit");
 struct CalLds {
   double table[CAL_TABLE];
@@ -48,62 +63,12 @@ struct CalLds {
   int st_e[CAL_STAGE];  // mass_sorted: with st_w the CAL_SORT_A grouped weights
   float st_w[CAL_STAGE];
   int part[CAL_WAVES];
+  int repeats;  // mass_sorted: a token names an expert twice
   int s_K;
 };
 
-// sets L.smass[e] = the mass of expert e (zero past E) and returns it in
-// thread e < E, from this thread's entries (key, weight) in the slices of
-// sort_dev.hpp; `sorted` (LDS) holds the weights grouped by expert
-template <int R>
-__device__ __forceinline__ double mass_of_entries(const int (&key)[R], const float (&rw)[R], int nr, int E,
-                                                  int key_bits, float* sorted, CalLds& L) {
-  const int tid = threadIdx.x, wv = tid >> 6;
-  int* wh = reinterpret_cast<int*>(L.table);  // [waves][E]
-  int cnt, first;
-  slice_scan<R>(key, nr, E, wh, E, L.part, cnt, first);
-  rank_rounds<R>(key, nr, E, key_bits, wh + wv * E, [&](int r, int pos, int) {
-    if (pos >= 0) sorted[pos] = rw[r];
-  });
-  __syncthreads();
-  double a = 0.0;
-  if (tid < E) {
-    // one dependent float64 chain per expert (the latency of the
-    // additions, not of the LDS reads, bounds it)
-#pragma unroll 8
-    for (int j = first; j < first + cnt; ++j) a += static_cast<double>(sorted[j]);
-    L.smass[tid] = a;
-  } else {
-    L.smass[tid] = 0.0;
-  }
-  if (tid < 32) L.smass[1024 + tid] = 0.0;
-  __syncthreads();
-  return a;
-}
-
-// the same for the n_all routing entries from idx + base (token-major), each
-// wavefront loading its own slice into registers
-__device__ __forceinline__ double mass_sorted(const int32_t* __restrict__ idx, const float* __restrict__ w, size_t base,
-                              int n_all, int E, int key_bits, CalLds& L) {
-  const int lane = threadIdx.x & 63;
-  const int nr = slice_rounds(n_all), lo = slice_lo(n_all, nr), hi = min(n_all, lo + nr * kWave);
-  double mass = 0.0;
-  with_rounds(nr, [&](auto RC) {
-    constexpr int R = decltype(RC)::value;
-    int key[R];
-    float rw[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int a = lo + r * kWave + lane;
-      const bool in = r < nr && a < hi;
-      key[r] = in ? idx[base + a] : -1;
-      rw[r] = in ? w[base + a] : 0.f;
-    }
-    mass = mass_of_entries<R>(key, rw, nr, E, key_bits, reinterpret_cast<float*>(L.st_e), L);
-  });
-  return mass;
-}
-
-// the same for the tokens [lo, hi), any size
+// The masses of the tokens [lo, hi), any size: sets L.smass[e] = the mass of
+// expert e (zero past E) and returns it in thread e < E.
 __device__ double mass_chunked(const int32_t* __restrict__ idx, const float* __restrict__ w, int lo, int hi,
                                int E, int k, CalLds& L) {
   const int tid = threadIdx.x;
@@ -169,6 +134,76 @@ __device__ double mass_chunked(const int32_t* __restrict__ idx, const float* __r
   if (tid < 32) L.smass[1024 + tid] = 0.0;
   __syncthreads();
   return acc;
+}
+
+// The same from this thread's entries (key, weight) in the slices of
+// sort_dev.hpp; `sorted` (LDS) holds the weights grouped by expert.
+// token_mask: the earlier lanes of this lane's token, where rounds hold whole
+// tokens and repeated experts are looked for (L.repeats is then set if a token
+// names an expert twice, and the masses are not what is wanted).
+template <int R>
+__device__ __forceinline__ double mass_of_entries(const int (&key)[R], const float (&rw)[R], int nr, int E,
+                                                  int key_bits, float* sorted, CalLds& L, uint64_t token_mask = 0) {
+  const int tid = threadIdx.x, wv = tid >> 6;
+  int* wh = reinterpret_cast<int*>(L.table);  // [waves][E]
+  uint64_t again = 0;
+  int cnt, first;
+  slice_scan<R>(key, nr, E, wh, E, L.part, cnt, first);
+  rank_rounds<R>(key, nr, E, key_bits, wh + wv * E, [&](int r, int pos, int, uint64_t peers) {
+    if (pos >= 0) sorted[pos] = rw[r];
+    again |= pos >= 0 ? peers & token_mask : 0;
+  });
+  if (again) L.repeats = 1;
+  __syncthreads();
+  double a = 0.0;
+  if (tid < E) {
+    // one dependent float64 chain per expert (the latency of the
+    // additions, not of the LDS reads, bounds it)
+#pragma unroll 8
+    for (int j = first; j < first + cnt; ++j) a += static_cast<double>(sorted[j]);
+    L.smass[tid] = a;
+  } else {
+    L.smass[tid] = 0.0;
+  }
+  if (tid < 32) L.smass[1024 + tid] = 0.0;
+  __syncthreads();
+  return a;
+}
+
+// The masses of the n_all routing entries of the tokens from lo_t on (where
+// cal_sorted() holds), each wavefront loading its own slice into registers.
+__device__ __forceinline__ double mass_sorted(const int32_t* __restrict__ idx, const float* __restrict__ w, int lo_t,
+                                              int n_all, int E, int k, int key_bits, CalLds& L) {
+  const int lane = threadIdx.x & 63;
+  const size_t base = (size_t)lo_t * k;
+  double mass = 0.0;
+  auto run = [&](auto RC, int W, int nr, uint64_t token_mask) {
+    constexpr int R = decltype(RC)::value;
+    const int lo = slice_lo(n_all, nr, W), hi = lane < W ? min(n_all, lo + nr * W) : 0;
+    int key[R];
+    float rw[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int a = lo + r * W + lane;
+      const bool in = r < nr && a < hi;
+      key[r] = in ? idx[base + a] : -1;
+      rw[r] = in ? w[base + a] : 0.f;
+    }
+    mass = mass_of_entries<R>(key, rw, nr, E, key_bits, reinterpret_cast<float*>(L.st_e), L, token_mask);
+  };
+  if (n_all <= CAL_STAGE) {
+    const int nr = slice_rounds(n_all);
+    with_rounds<DS_R / 2>(nr, [&](auto RC) { run(RC, kWave, nr, 0); });
+  } else {
+    // beyond CAL_STAGE entries: rounds of whole tokens (64 entries where k
+    // divides 64), so that a token's repeated experts meet in one round
+    if (threadIdx.x == 0) L.repeats = 0;  // (slice_scan's barriers order it before the ranks)
+    const int W = kWave / k * k;
+    run(std::integral_constant<int, DS_R>{}, W, slice_rounds(n_all, W),
+        ((1ull << lane) - 1) & ~((1ull << (lane - lane % k)) - 1));
+    if (L.repeats) mass = mass_chunked(idx, w, lo_t, lo_t + n_all / k, E, k, L);
+  }
+  return mass;
 }
 
 // K = max(k, the first K with c_K >= p * c_E) from L.smass, in every thread.

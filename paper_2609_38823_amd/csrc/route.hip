@@ -369,7 +369,7 @@ __global__ __launch_bounds__(CAL_THREADS) void calibrate_route_kernel(
   if (guard_skip(g)) return;
   __shared__ CalLds L;
   __shared__ int s_last;
-  const double a = mass_sorted(idx_full, w_full, 0, T * k, E, key_bits, L);
+  const double a = mass_sorted(idx_full, w_full, 0, T * k, E, k, key_bits, L);
   const int K = prefix_K(E, k, p, L);
   const int tid = threadIdx.x;
   if (blockIdx.x == 0) {
@@ -513,7 +513,7 @@ __global__ __launch_bounds__(CAL_THREADS) void route_small_kernel(
 // workgroup included (12 248 entries, E 128: 36 us, where masses, re-route,
 // histogram, ranks and the FFN's clearing launch took 68).
 bool calibrate_route_fused(int T, int E, int k) {
-  return T >= 1 && (size_t)T * k <= (size_t)CAL_SORT_A && E <= CAL_SORT_E;
+  return T >= 1 && cal_sorted((size_t)T * k, E, k);
 }
 
 hipError_t launch_calibrate_route(const float* logits, const int32_t* idx_full, const float* w_full,

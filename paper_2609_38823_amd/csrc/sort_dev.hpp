@@ -16,20 +16,23 @@ constexpr int DS_WAVES = DS_THREADS / kWave;
 constexpr int DS_R = 16;                      // rounds of 64 entries per wavefront
 constexpr int DS_MAX = DS_THREADS * DS_R;     // entries it can hold
 
-// The wavefronts take contiguous slices in entry order, in rounds of 64:
+// The wavefronts take contiguous slices in entry order, in rounds of W <= 64:
 // rounds per wavefront (the same for all) for A entries, and the first entry
 // of this thread's wavefront.
-__device__ __forceinline__ int slice_rounds(int A) { return ((A + DS_WAVES - 1) / DS_WAVES + kWave - 1) / kWave; }
-__device__ __forceinline__ int slice_lo(int A, int nr) {
-  return min(A, (int)(threadIdx.x >> 6) * nr * kWave);
+__device__ __forceinline__ int slice_rounds(int A, int W = kWave) {
+  return ((A + DS_WAVES - 1) / DS_WAVES + W - 1) / W;
+}
+__device__ __forceinline__ int slice_lo(int A, int nr, int W = kWave) {
+  return min(A, (int)(threadIdx.x >> 6) * nr * W);
 }
 
 // Ranks of this wavefront's entries, in order: lanes with the same key are
 // found with ballots over the key bits, a popcount gives each its rank, and
 // `run` (this wavefront's next position per expert, in LDS) advances from
 // round to round.  The ballots of four rounds are formed together, ahead of
-// the chain through `run` (8192 entries: the whole sort 10.3 -> 8.6 us).  emit(round, position, key)
-// is called with position -1 for keys outside [0, E).
+// the chain through `run` (8192 entries: the whole sort 10.3 -> 8.6 us).
+// emit(round, position, key, lanes of this round with the same key) is called
+// with position -1 for keys outside [0, E).
 template <int R, class Emit>
 __device__ __forceinline__ void rank_rounds(const int (&key)[R], int nr, int E, int key_bits, int* run, Emit emit) {
   const int lane = threadIdx.x & 63;
@@ -60,7 +63,7 @@ __device__ __forceinline__ void rank_rounds(const int (&key)[R], int nr, int E, 
         if ((63 - __clzll(peers[q])) == lane) run[e] = at + __popcll(peers[q]);
       }
       __builtin_amdgcn_wave_barrier();
-      emit(r0 + q, pos, e);
+      emit(r0 + q, pos, e, peers[q]);
     }
   }
 }
@@ -107,16 +110,16 @@ __device__ __forceinline__ void slice_scan(const int (&key)[R], int nr, int E, i
   __syncthreads();
 }
 
-// f(R) with R = the smallest of 1, 4 and DS_R rounds that hold nr: short
-// slices pay for no rounds that they do not have (256 entries: sort 3.9 -> 2.0 us)
-template <class F>
+// f(R) with R = the smallest of 1, 4 and MAX rounds that hold nr: short slices
+// pay for no rounds that they do not have (256 entries: sort 3.9 -> 2.0 us)
+template <int MAX, class F>
 __device__ __forceinline__ void with_rounds(int nr, F f) {
   if (nr <= 1)
     f(std::integral_constant<int, 1>{});
   else if (nr <= 4)
     f(std::integral_constant<int, 4>{});
   else
-    f(std::integral_constant<int, DS_R>{});
+    f(std::integral_constant<int, MAX>{});
 }
 
 // All DS_THREADS threads call it.  keys[a] is the expert of entry a (global
@@ -141,7 +144,7 @@ __device__ __forceinline__ void sort_rounds(const int32_t* keys, int A, int E, i
     offsets[tid] = first;
     if (tid == E - 1) offsets[E] = first + cnt;
   }
-  rank_rounds<R>(key, nr, E, key_bits, wh + wv * E, [&](int r, int pos, int) {
+  rank_rounds<R>(key, nr, E, key_bits, wh + wv * E, [&](int r, int pos, int, uint64_t) {
     const int a = lo + r * kWave + lane;
     if (a >= hi) return;
     row_of_slot[a] = pos;
@@ -152,7 +155,7 @@ __device__ __forceinline__ void sort_rounds(const int32_t* keys, int A, int E, i
 __device__ __forceinline__ void sort_small(const int32_t* keys, int A, int E, int key_bits, int* wh, int* part,
                            int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
                            int32_t* __restrict__ src_of_row, int32_t* __restrict__ row_of_slot) {
-  with_rounds(slice_rounds(A), [&](auto RC) {
+  with_rounds<DS_R>(slice_rounds(A), [&](auto RC) {
     sort_rounds<decltype(RC)::value>(keys, A, E, key_bits, wh, part, counts, offsets, src_of_row, row_of_slot);
   });
 }

@@ -393,6 +393,55 @@ def test_calibrate_skips_out_of_range_entries(T, E, k):
     np.testing.assert_array_equal(host(order), ro)
 
 
+@pytest.mark.parametrize("T,E,k", [
+    (1024, 128, 8),  # 8192 entries: the weights of a repeated expert one by one
+    (1025, 128, 8),  # beyond: summed within the token first
+    (2048, 100, 8),  # the sorted masses' last size at k = 8
+    (2560, 64, 6),   # 15 360 entries: their last size at k = 6 (rounds of 60 entries)
+    (2561, 64, 6),   # the chunked masses
+    (4097, 32, 3),   # rounds of 63 entries
+    (500, 300, 17),  # rounds of 51 entries
+    (2049, 128, 8),  # the chunked masses
+    (1025, 600, 8),  # E > 512: always chunked
+])
+def test_calibrate_repeated_expert(T, E, k):
+    """Tokens that name an expert twice.  The busiest experts' sums start at
+    2^30 and every later weight is 3/8 of a unit in their last place: two of
+    them vanish when they are added one by one (up to 8192 entries) and move
+    the sum by one unit when they are summed first (beyond)."""
+    rng = np.random.default_rng(T * k)
+    idx, _ = I.synthetic_routing(T, E, k, seed=T + k)
+    w = np.full((T, k), 1.5 * 2.0 ** -24, np.float32)
+    w[0] = 2.0 ** 30
+    idx[0] = np.argsort(-np.bincount(idx.ravel(), minlength=E), kind="stable")[:k]
+    for t in range(1, T):
+        if t % 3:
+            a, b = rng.choice(k, 2, replace=False)
+            idx[t, a] = idx[t, b]
+    first = T * k > 8192 or E > 512
+    ref = np.zeros(E)
+    for t in range(T):
+        if first:
+            cell = {}
+            for e, v in zip(idx[t].tolist(), w[t].tolist()):
+                cell[e] = cell.get(e, 0.0) + v
+            for e, v in cell.items():
+                ref[e] += v
+        else:
+            for e, v in zip(idx[t].tolist(), w[t].tolist()):
+                ref[e] += v
+    assert ref.max() > 2.0 ** 30 if first else ref.max() == 2.0 ** 30
+    mass = torch.full((1, E), float("nan"), dtype=torch.float64, device="cuda")
+    K = i32((1,))
+    abi.moe_calibrate_prefix(dev(idx), dev(w), E, 0.9, mass, ws_for(T, E, k, 8), K_out=K)
+    np.testing.assert_array_equal(host(mass)[0].view(np.uint64), ref.view(np.uint64))
+    mass2, K2 = torch.full_like(mass, -1.0), i32((1,))
+    abi.moe_calibrate_route_prefix(dev(I.synthetic_rows(T, E, "f32", seed=3)), dev(idx), dev(w), 0.9, mass2, K2,
+                                   i32((T, k)), f32((T, k)))
+    np.testing.assert_array_equal(host(mass2).view(np.uint64), host(mass).view(np.uint64))
+    assert int(host(K)[0]) == int(host(K2)[0]) == int(oracle.prefix_length(ref, 0.9, k))
+
+
 def test_combine_skips_out_of_range_rows():
     """Slots whose row index lies outside [0, T*k) contribute nothing: the
     output equals the oracle's combine with those slots' weights at zero."""
