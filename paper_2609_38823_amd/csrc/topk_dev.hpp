@@ -17,7 +17,7 @@ namespace {
 // vector units.  High word: the float's bits mapped to unsigned order (-0 as
 // +0); low word: 0x7fffffff - e.  Key 0: taken, absent or NaN (never chosen
 // while a candidate is left; reads back as -inf, 0x7fffffff).
-// (Eight rounds over 128 experts, one row of 16 lanes per token: 3.8 -> 2.4 us.)
+// (Top-k of 64 tokens, E 128, k 8, one wavefront per token: 4.4 -> 3.6 us.)
 typedef unsigned long long tkey;
 __device__ __forceinline__ tkey topk_key(float v, int e) {
   uint32_t u = __float_as_uint(v + 0.f);
@@ -32,6 +32,26 @@ __device__ __forceinline__ float key_value(tkey q) {
   return q ? v : -INFINITY;
 }
 __device__ __forceinline__ tkey key_max(tkey a, tkey b) { return a > b ? a : b; }
+
+// The same order for more than TOPK_KEYS values per lane, where the selection is
+// bound by its instructions and 64-bit compares are slow: the float mapped to a
+// signed int, its maximum first and then the lowest index that holds it.
+// TOPK_NONE: taken, absent or NaN.  (8192 tokens on given logits, one row of 16
+// lanes per token, against keys: E 128, k 8 5.1 -> 4.3 us; E 256, k 16 20.4 ->
+// 8.6; one wavefront per token, E 512, k 8: 19.4 -> 14.7.  Up to TOPK_KEYS
+// values a round is one chain of DPP moves instead of two.)
+constexpr int TOPK_KEYS = 4;
+constexpr int TOPK_NONE = -0x7fffffff - 1;
+__device__ __forceinline__ int topk_ord(float v) {
+  int s = __float_as_int(v + 0.f);
+  s ^= (s >> 31) & 0x7fffffff;
+  return v == v ? s : TOPK_NONE;
+}
+__device__ __forceinline__ tkey ord_key(int s, int e) {  // as topk_key
+  return s == TOPK_NONE ? 0ull
+                        : (static_cast<tkey>(static_cast<uint32_t>(s) ^ 0x80000000u) << 32) |
+                              static_cast<uint32_t>(0x7fffffff - e);
+}
 
 // the best key of a row of 16 lanes in all its lanes, by DPP moves (quad
 // swaps, then the half-row and row mirrors pair the groups); the wavefront's
@@ -66,6 +86,68 @@ __device__ __forceinline__ tkey wave_best(tkey q) {
   }
   return best;
 }
+template <int CTRL>
+__device__ __forceinline__ int dpp_i(int v) {
+  return __builtin_amdgcn_mov_dpp(v, CTRL, 0xF, 0xF, false);
+}
+__device__ __forceinline__ int row_max(int v) {
+  v = max(v, dpp_i<0xB1>(v));
+  v = max(v, dpp_i<0x4E>(v));
+  v = max(v, dpp_i<0x141>(v));
+  return max(v, dpp_i<0x140>(v));
+}
+__device__ __forceinline__ int row_min(int v) {
+  v = min(v, dpp_i<0xB1>(v));
+  v = min(v, dpp_i<0x4E>(v));
+  v = min(v, dpp_i<0x141>(v));
+  return min(v, dpp_i<0x140>(v));
+}
+
+// One lane's candidates (value c is expert j + STRIDE c) and their rounds: best()
+// returns the best one of the row of 16 lanes (STRIDE 16) or of the wavefront
+// (STRIDE 64) and takes it out.
+template <int MAXC, int STRIDE, bool KEYS = (MAXC <= TOPK_KEYS)>
+struct Candidates {
+  tkey q[MAXC];
+  __device__ __forceinline__ void set(int c, float v, int e, bool in) { q[c] = in ? topk_key(v, e) : 0ull; }
+  __device__ __forceinline__ tkey best(int) {
+    tkey b = q[0];
+#pragma unroll
+    for (int c = 1; c < MAXC; ++c) b = key_max(b, q[c]);
+    b = STRIDE == 16 ? row_best(b) : wave_best(b);
+#pragma unroll
+    for (int c = 0; c < MAXC; ++c) q[c] = q[c] == b ? 0ull : q[c];
+    return b;
+  }
+};
+template <int MAXC, int STRIDE>
+struct Candidates<MAXC, STRIDE, false> {
+  int s[MAXC];
+  __device__ __forceinline__ void set(int c, float v, int, bool in) { s[c] = in ? topk_ord(v) : TOPK_NONE; }
+  __device__ __forceinline__ tkey best(int j) {
+    int b = s[0];
+#pragma unroll
+    for (int c = 1; c < MAXC; ++c) b = max(b, s[c]);
+    b = row_max(b);
+    if (STRIDE == 64)
+      b = max(max(__builtin_amdgcn_readlane(b, 0), __builtin_amdgcn_readlane(b, 16)),
+              max(__builtin_amdgcn_readlane(b, 32), __builtin_amdgcn_readlane(b, 48)));
+    int lo = 0x7fffffff, hi = 0x7fffffff;  // two chains
+#pragma unroll
+    for (int c = MAXC / 2 - 1; c >= 0; --c) {
+      lo = s[c] == b ? j + STRIDE * c : lo;
+      hi = s[c + MAXC / 2] == b ? j + STRIDE * (c + MAXC / 2) : hi;
+    }
+    int e = row_min(min(lo, hi));
+    if (STRIDE == 64)
+      e = min(min(__builtin_amdgcn_readlane(e, 0), __builtin_amdgcn_readlane(e, 16)),
+              min(__builtin_amdgcn_readlane(e, 32), __builtin_amdgcn_readlane(e, 48)));
+#pragma unroll
+    for (int c = 0; c < MAXC; ++c) s[c] = j + STRIDE * c == e ? TOPK_NONE : s[c];
+    return ord_key(b, e);
+  }
+};
+
 // sum over the wavefront: row sums by DPP, then the four rows in order
 __device__ __forceinline__ float wave_sum(float v) {
   v += dpp_f<0xB1>(v);
@@ -83,20 +165,12 @@ __device__ __forceinline__ float wave_sum(float v) {
 template <int MAXC>  // values per lane: E <= 64 MAXC
 __device__ __forceinline__ void topk_select_vals(const float (&vals)[MAXC], int E, int k, int Klim, int lane,
                                                  int32_t* idx_t, float* w_t) {
-  tkey q[MAXC];
+  Candidates<MAXC, 64> cand;
 #pragma unroll
-  for (int c = 0; c < MAXC; ++c) {
-    const int e = lane + c * 64;
-    q[c] = e < Klim ? topk_key(vals[c], e) : 0ull;
-  }
+  for (int c = 0; c < MAXC; ++c) cand.set(c, vals[c], lane + c * 64, lane + c * 64 < Klim);
   tkey mine = 0;
   for (int r = 0; r < k; ++r) {
-    tkey best = q[0];
-#pragma unroll
-    for (int c = 1; c < MAXC; ++c) best = key_max(best, q[c]);
-    best = wave_best(best);
-#pragma unroll
-    for (int c = 0; c < MAXC; ++c) q[c] = q[c] == best ? 0ull : q[c];
+    const tkey best = cand.best(lane);
     if (lane == r) mine = best;
   }
   const float my_v = key_value(mine);
@@ -135,28 +209,20 @@ __device__ __forceinline__ float row_sum(float v) {
 
 // The k best of one token's logits [0, Klim) held by the 16 lanes of a row:
 // lane j holds experts j, j + 16, ... in v[c] (expert j + 16 c).  Each
-// round's arg-max is a lane-local scan plus row_best; round r's winner is
+// round's arg-max is a lane-local scan plus DPP moves within the row; round r's winner is
 // kept by lane r % 16 in slot r / 16 (k <= 32).  Same selection order, tie
 // rule and weights as topk_select_vals: the slots' exponentials are summed
 // by the same butterfly, so for k <= 16 the weights are bitwise equal.
 template <int MAXC>
 __device__ __forceinline__ void row_topk_select(const float (&v)[MAXC], int j, int E, int k, int Klim,
                                                 int32_t* idx_t, float* w_t) {
-  tkey cq[MAXC];
+  Candidates<MAXC, 16> cand;
 #pragma unroll
-  for (int c = 0; c < MAXC; ++c) {
-    const int e = j + 16 * c;
-    cq[c] = e < Klim ? topk_key(v[c], e) : 0ull;
-  }
+  for (int c = 0; c < MAXC; ++c) cand.set(c, v[c], j + 16 * c, j + 16 * c < Klim);
   tkey mine[2] = {0, 0};
   float v0 = 0.f;
   for (int r = 0; r < k; ++r) {
-    tkey best = cq[0];
-#pragma unroll
-    for (int c = 1; c < MAXC; ++c) best = key_max(best, cq[c]);
-    best = row_best(best);
-#pragma unroll
-    for (int c = 0; c < MAXC; ++c) cq[c] = cq[c] == best ? 0ull : cq[c];
+    const tkey best = cand.best(j);
     if (r == 0) v0 = key_value(best);
     if ((r & 15) == j) mine[r >> 4] = best;
   }

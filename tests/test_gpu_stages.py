@@ -121,6 +121,53 @@ def test_topk_on_given_logits(T, E, k, ties):
     np.testing.assert_allclose(host(w), ref_w, rtol=1e-5, atol=1e-7)
 
 
+# one wavefront per token with 2, 4 and 16 values per lane, one row of 16 lanes
+# per token with 8 and 16, k at and past the count of selectable logits
+@pytest.mark.parametrize("T,E,k", [(70, 16, 8), (70, 128, 32), (300, 250, 16), (40, 600, 8), (4099, 128, 8),
+                                   (4100, 200, 20), (35, 1024, 32)])
+def test_topk_special_logits(T, E, k):
+    """NaN, infinite and signed-zero logits.  Values descend, equal ones by
+    index (-0 equal to +0); a NaN is never selected, and slots left over hold
+    index 2^31 - 1 at -inf.  Weights follow the float softmax of the selected
+    values: NaN where the largest is infinite."""
+    rng = np.random.default_rng(T + E + k)
+    a = rng.standard_normal((T, E)).astype(np.float32)
+    u = rng.random((T, E))
+    kind = np.arange(T) % 7
+    inf = np.float32(np.inf)
+    a[kind == 0] = np.nan
+    a[kind == 1] = -inf
+    a[(kind == 2)[:, None] & (u > 0.02)] = -inf  # fewer finite values than k
+    a[(kind == 3)[:, None] & (u > 0.02)] = np.nan
+    a[(kind == 4)[:, None] & (u > 0.9)] = inf
+    z = (kind == 5)[:, None]
+    a[z & (u < 0.5)] = 0.0
+    a[z & (u < 0.25)] = -0.0
+    a[z & (u > 0.8)] = -1.0
+    cand = np.where(np.isnan(a), -inf, a) + np.float32(0.0)
+    # NaN last, then value descending, index ascending
+    order = np.lexsort((np.broadcast_to(np.arange(E), a.shape), -cand, np.isnan(a)), axis=1)[:, :k]
+    idx_ref = np.where(np.take_along_axis(np.isnan(a), order, 1), 0x7fffffff, order)
+    v = np.where(idx_ref == 0x7fffffff, -inf, np.take_along_axis(cand, order, 1)).astype(np.float64)
+    with np.errstate(invalid="ignore"):
+        ex = np.exp(v - v[:, :1])
+        w_ref = ex / ex.sum(1, keepdims=True)
+    logits, idx, w = dev(a), i32((T, k)), f32((T, k))
+    abi.moe_route(None, None, None, k, logits, idx, w)
+    np.testing.assert_array_equal(host(idx), idx_ref)
+    np.testing.assert_allclose(host(w), w_ref, rtol=1e-5, atol=1e-30)
+    # the prefix re-route reads the same selection from registers
+    K, mass, idx2, w2 = i32((1,)), torch.empty((1, E), dtype=torch.float64, device="cuda"), i32((T, k)), f32((T, k))
+    ident = np.tile(np.arange(k, dtype=np.int32), (T, 1))
+    full = np.full((T, k), 1e-30, np.float32)
+    full[0, k - 1] = 1.0
+    ident[0, k - 1] = E - 1  # the last expert holds the mass: K = E
+    abi.moe_calibrate_route_prefix(logits, dev(ident), dev(full), 1.0, mass, K, idx2, w2)
+    assert int(host(K)[0]) == E
+    np.testing.assert_array_equal(host(idx2), host(idx))
+    np.testing.assert_allclose(host(w2), w_ref, rtol=1e-5, atol=1e-30)
+
+
 @pytest.mark.parametrize("T,E,k,segs,Ks", [
     (512, 16, 2, [0, 512], [9]),
     (512, 128, 8, [0, 512], [84]),
