@@ -5,8 +5,8 @@
 //            rows split over blockIdx.y (each split sums its rows in order)
 //   mlp      every workgroup forms the feature x = [sum / (n - 1); row n - 1]
 //            in LDS (the splits added in order, then one scaling) while its
-//            first weights are on their way, and each wavefront one hidden
-//            unit relu(W1[u] . x + b1[u]); the last workgroup to finish forms
+//            first weights are on their way, and each wavefront hidden units
+//            relu(W1[u] . x + b1[u]); the last workgroup to finish forms
 //            the two class logits, p_exit = softmax(z)_1 and the exit flag
 //            p_exit >= theta (compared in float64)
 // Every sum has a fixed order, so the gate is deterministic.  The gate is
@@ -15,10 +15,19 @@
 // hidden units, and the drop behind it: 32.5 -> 26.5 us.
 #include "common.hpp"
 
+#include <algorithm>
+
 namespace decomoe {
 namespace {
 
 constexpr int SG_ROWS = 32;  // rows per pooling split until there are 16 splits
+// Workgroups of savb_mlp_kernel: each forms the feature and adds one count at
+// the one address, so beyond a few hundred hidden units the wavefronts take
+// several units each (512 rows, d 256, 8192 units: 62 us with one unit per
+// wavefront, 30 with 256 workgroups; four launches with the feature formed
+// once took 40.  d 2048, 2048 units: 23.0, 21.4 and 28.2; d 8192, 8192 units:
+// 161, 126 and 211.  128 or 512 workgroups: d 2048, 2048 units 23.8, 23.0).
+constexpr unsigned SG_WGS = 256;
 
 int savb_splits(int n) {
   const int rows = n - 1;
@@ -61,7 +70,8 @@ __device__ __forceinline__ float last_row(const void* rows, int n, int d, int c)
               : static_cast<const float*>(rows)[(size_t)(n - 1) * d + c];
 }
 
-template <bool BF16>
+// PRE: 16-byte weight loads per lane that are in flight ahead of a unit
+template <bool BF16, int PRE>
 __global__ __launch_bounds__(256) void savb_mlp_kernel(
     const void* __restrict__ rows, int n, int d, int splits, const float* __restrict__ partial,
     float* __restrict__ feature, const float* __restrict__ w1, const float* __restrict__ b1, int hid,
@@ -71,20 +81,25 @@ __global__ __launch_bounds__(256) void savb_mlp_kernel(
   if (guard_skip(g)) return;
   extern __shared__ __attribute__((aligned(16))) float xs[];  // [2d], 64 KB at d = 8192: the last steps reuse it
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int u = blockIdx.x * 4 + wv;
-  const float* wr = w1 + (size_t)min(u, hid - 1) * 2 * d;
   // 16-byte weight loads: lane l takes columns 4 (l + 64 j) .. + 4 for j = 0,
-  // 1, ...; the first PRE of them are issued before x is formed
-  constexpr int PRE = 16;
-  const bool vec = (d & 127) == 0 && (reinterpret_cast<uintptr_t>(wr) & 15) == 0;
-  const float4* w4 = reinterpret_cast<const float4*>(wr);
+  // 1, ...; the first PRE of a unit (and its bias) are issued before x is
+  // formed, or before the previous unit's are used
+  const bool vec = (d & 127) == 0 && (reinterpret_cast<uintptr_t>(w1) & 15) == 0;
   const int n4 = (2 * d) >> 2;
   float4 v[PRE];
+  float bu = 0.f;
+  auto first_weights = [&](int u) {
+    u = min(u, hid - 1);
+    const float4* w4 = reinterpret_cast<const float4*>(w1 + (size_t)u * 2 * d);
+    if (b1) bu = b1[u];
 #pragma unroll
-  for (int q = 0; q < PRE; ++q) {
-    const int j = lane + 64 * q;
-    v[q] = vec && j < n4 ? w4[j] : make_float4(0.f, 0.f, 0.f, 0.f);
-  }
+    for (int q = 0; q < PRE; ++q) {
+      const int j = lane + 64 * q;
+      v[q] = vec && j < n4 ? w4[j] : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+  };
+  first_weights(blockIdx.x * 4 + wv);
+  const float bz = b2 ? b2[wv & 1] : 0.f;
   const float inv = n > 1 ? 1.f / static_cast<float>(n - 1) : 0.f;
   if ((d & 3) == 0) {  // the partials' rows are whole 16-byte vectors (the workspace is 16-byte aligned)
     for (int c = 4 * tid; c < d; c += 1024) {
@@ -118,8 +133,14 @@ __global__ __launch_bounds__(256) void savb_mlp_kernel(
   __syncthreads();
   if (feature && blockIdx.x == 0)
     for (int c = tid; c < 2 * d; c += 256) feature[c] = xs[c];
-  if (u < hid) {
+  for (int u = blockIdx.x * 4 + wv; u < hid; u += gridDim.x * 4) {
+    const float* wr = w1 + (size_t)u * 2 * d;
     float acc = 0.f;
+    const float b = bu;
+    float4 c[PRE];
+#pragma unroll
+    for (int q = 0; q < PRE; ++q) c[q] = v[q];
+    if (u + (int)gridDim.x * 4 < hid) first_weights(u + gridDim.x * 4);
     auto add4 = [&](const float4& w, int j) {
       const float4 x = *reinterpret_cast<const float4*>(xs + 4 * j);
       acc = fmaf(w.x, x.x, acc);
@@ -128,9 +149,10 @@ __global__ __launch_bounds__(256) void savb_mlp_kernel(
       acc = fmaf(w.w, x.w, acc);
     };
     if (vec) {
+      const float4* w4 = reinterpret_cast<const float4*>(wr);
 #pragma unroll
       for (int q = 0; q < PRE; ++q)
-        if (lane + 64 * q < n4) add4(v[q], lane + 64 * q);
+        if (lane + 64 * q < n4) add4(c[q], lane + 64 * q);
       for (int j0 = lane + 64 * PRE; j0 < n4; j0 += 64 * 8) {  // eight loads in flight
         float4 r[8];
 #pragma unroll
@@ -140,13 +162,20 @@ __global__ __launch_bounds__(256) void savb_mlp_kernel(
           if (j0 + 64 * q < n4) add4(r[q], j0 + 64 * q);
       }
     } else {
-      for (int c = lane; c < 2 * d; c += 64) acc = fmaf(wr[c], xs[c], acc);
+      for (int c0 = lane; c0 < 2 * d; c0 += 64 * 16) {  // sixteen loads in flight
+        float r[16];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) r[q] = wr[min(c0 + 64 * q, 2 * d - 1)];
+#pragma unroll
+        for (int q = 0; q < 16; ++q)
+          if (c0 + 64 * q < 2 * d) acc = fmaf(r[q], xs[c0 + 64 * q], acc);
+      }
     }
     // lanes in order: the sum of lane partials is formed by lane 0
     for (int off = 32; off >= 1; off >>= 1) acc += __shfl_down(acc, off, 64);
     // agent scope: the deciding workgroup may run on another XCD
     if (lane == 0)
-      __hip_atomic_store(hidden + u, fmaxf(acc + (b1 ? b1[u] : 0.f), 0.f), __ATOMIC_RELAXED,
+      __hip_atomic_store(hidden + u, fmaxf(acc + b, 0.f), __ATOMIC_RELAXED,
                          __HIP_MEMORY_SCOPE_AGENT);
   }
   // every unit of the workgroup is stored (vmcnt 0), then it counts itself;
@@ -161,11 +190,20 @@ __global__ __launch_bounds__(256) void savb_mlp_kernel(
   float* z = xs;
   if (wv < 2) {  // class = wavefront
     float acc = 0.f;
-    for (int h = lane; h < hid; h += 64)
-      acc = fmaf(w2[(size_t)wv * hid + h],
-                 __hip_atomic_load(hidden + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), acc);
+    for (int h0 = lane; h0 < hid; h0 += 64 * 8) {  // eight loads in flight, added in order
+      float hv[8], wq[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const int h = min(h0 + 64 * q, hid - 1);
+        hv[q] = __hip_atomic_load(hidden + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        wq[q] = w2[(size_t)wv * hid + h];
+      }
+#pragma unroll
+      for (int q = 0; q < 8; ++q)
+        if (h0 + 64 * q < hid) acc = fmaf(wq[q], hv[q], acc);
+    }
     for (int off = 32; off >= 1; off >>= 1) acc += __shfl_down(acc, off, 64);
-    if (lane == 0) z[wv] = acc + (b2 ? b2[wv] : 0.f);
+    if (lane == 0) z[wv] = acc + bz;
   }
   __syncthreads();
   if (tid == 0) {
@@ -226,14 +264,17 @@ hipError_t launch_savb_gate(const void* rows, bool bf16, int n, int d, const flo
     savb_pool_kernel<false><<<grid, 256, 0, s>>>(rows, n, d, per, partial, ctr, g);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const unsigned hb = (unsigned)((hid + 3) / 4);
+  const unsigned hb = std::min(SG_WGS, (unsigned)((hid + 3) / 4));
   const size_t lds = (size_t)2 * d * sizeof(float);
-  if (bf16)
-    savb_mlp_kernel<true><<<hb, 256, lds, s>>>(rows, n, d, splits, partial, feature, w1, b1, hid, hidden, w2, b2,
-                                               theta, p_exit, exit_flag, exit_layer, layer, ctr, g);
-  else
-    savb_mlp_kernel<false><<<hb, 256, lds, s>>>(rows, n, d, splits, partial, feature, w1, b1, hid, hidden, w2, b2,
-                                                theta, p_exit, exit_flag, exit_layer, layer, ctr, g);
+#define SAVB_MLP(BF16, PRE)                                                                                      \
+  savb_mlp_kernel<BF16, PRE><<<hb, 256, lds, s>>>(rows, n, d, splits, partial, feature, w1, b1, hid, hidden, w2, b2, \
+                                                  theta, p_exit, exit_flag, exit_layer, layer, ctr, g)
+  if (d <= 512) {
+    if (bf16) SAVB_MLP(true, 4); else SAVB_MLP(false, 4);
+  } else {
+    if (bf16) SAVB_MLP(true, 16); else SAVB_MLP(false, 16);
+  }
+#undef SAVB_MLP
   return hipGetLastError();
 }
 

@@ -79,9 +79,12 @@ def test_savb_gate(n, d, dt):
 
 # the feature in LDS (64 KB at d = 8192), vector and element loads of the
 # weights and partials, weights beyond the first 16 loads of a lane, one
-# hidden unit, a last workgroup that is not full, no preceding rows
+# hidden unit, a last workgroup that is not full, no preceding rows; beyond
+# 1024 units (256 workgroups) several units per wavefront
 @pytest.mark.parametrize("n,d,hid,dt", [(3, 8192, 5, "bf16"), (40, 2176, 1, "f32"), (1, 128, 7, "bf16"),
-                                        (70, 3, 9, "f32"), (2, 1, 1, "f32"), (33, 100, 600, "bf16")])
+                                        (70, 3, 9, "f32"), (2, 1, 1, "f32"), (33, 100, 600, "bf16"),
+                                        (20, 256, 1024, "bf16"), (20, 256, 1025, "f32"), (35, 640, 2051, "bf16"),
+                                        (9, 2176, 1030, "f32"), (1, 512, 4099, "bf16"), (66, 1000, 2050, "f32")])
 def test_savb_gate_edges(n, d, hid, dt):
     rng = np.random.default_rng(n + d + hid)
     rows = I.synthetic_rows(n, d, dt, seed=d)
