@@ -29,41 +29,59 @@ __device__ __forceinline__ int slice_lo(int A, int nr, int W = kWave) {
 // Ranks of this wavefront's entries, in order: lanes with the same key are
 // found with ballots over the key bits, a popcount gives each its rank, and
 // `run` (this wavefront's next position per expert, in LDS) advances from
-// round to round.  The ballots of four rounds are formed together, ahead of
-// the chain through `run` (8192 entries: the whole sort 10.3 -> 8.6 us).
+// round to round.  The ballots of up to four rounds are formed together, ahead
+// of the chain through `run` (8192 entries: the whole sort 10.3 -> 8.6 us);
+// the last rounds are not filled up to four (2048 entries, two rounds, the whole
+// sort with 1024 experts: 7.3 -> 6.4 us).
 // emit(round, position, key, lanes of this round with the same key) is called
 // with position -1 for keys outside [0, E).
-template <int R, class Emit>
-__device__ __forceinline__ void rank_rounds(const int (&key)[R], int nr, int E, int key_bits, int* run, Emit emit) {
+template <int R0, int Q, int R, class Emit>
+__device__ __forceinline__ void rank_group(const int (&key)[R], int E, int key_bits, int* run, Emit& emit) {
   const int lane = threadIdx.x & 63;
   const uint64_t lt_mask = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-  constexpr int Q = R < 4 ? R : 4;
+  uint64_t peers[Q];
 #pragma unroll
-  for (int r0 = 0; r0 < R; r0 += Q) {
-    if (r0 >= nr) break;
-    uint64_t peers[Q];
-#pragma unroll
-    for (int q = 0; q < Q; ++q) peers[q] = __ballot(key[r0 + q] >= 0 && key[r0 + q] < E);
+  for (int q = 0; q < Q; ++q) peers[q] = __ballot(key[R0 + q] >= 0 && key[R0 + q] < E);
 #pragma unroll 1
-    for (int b = 0; b < key_bits; ++b)
-#pragma unroll
-      for (int q = 0; q < Q; ++q) {
-        const bool bit = (key[r0 + q] >> b) & 1;
-        const uint64_t m = __ballot(bit);
-        peers[q] &= bit ? m : ~m;
-      }
+  for (int b = 0; b < key_bits; ++b)
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
-      const int e = key[r0 + q];
-      int pos = -1;
-      if (e >= 0 && e < E) {
-        const int at = run[e];
-        pos = at + __popcll(peers[q] & lt_mask);
-        // the highest lane of the group advances the expert's counter
-        if ((63 - __clzll(peers[q])) == lane) run[e] = at + __popcll(peers[q]);
-      }
-      __builtin_amdgcn_wave_barrier();
-      emit(r0 + q, pos, e, peers[q]);
+      const bool bit = (key[R0 + q] >> b) & 1;
+      const uint64_t m = __ballot(bit);
+      peers[q] &= bit ? m : ~m;
+    }
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int e = key[R0 + q];
+    int pos = -1;
+    if (e >= 0 && e < E) {
+      const int at = run[e];
+      pos = at + __popcll(peers[q] & lt_mask);
+      // the highest lane of the group advances the expert's counter
+      if ((63 - __clzll(peers[q])) == lane) run[e] = at + __popcll(peers[q]);
+    }
+    __builtin_amdgcn_wave_barrier();
+    emit(R0 + q, pos, e, peers[q]);
+  }
+}
+template <int R, int R0 = 0, class Emit>
+__device__ __forceinline__ void rank_rounds(const int (&key)[R], int nr, int E, int key_bits, int* run, Emit emit) {
+  if constexpr (R0 < R) {
+    const int left = nr - R0;
+    if (left <= 0) return;
+    if constexpr (R - R0 < 4) {
+      rank_group<R0, 1>(key, E, key_bits, run, emit);
+      rank_rounds<R, R0 + 1>(key, nr, E, key_bits, run, emit);
+    } else {
+      if (left == 1)
+        rank_group<R0, 1>(key, E, key_bits, run, emit);
+      else if (left == 2)
+        rank_group<R0, 2>(key, E, key_bits, run, emit);
+      else if (left == 3)
+        rank_group<R0, 3>(key, E, key_bits, run, emit);
+      else
+        rank_group<R0, 4>(key, E, key_bits, run, emit);
+      rank_rounds<R, R0 + 4>(key, nr, E, key_bits, run, emit);
     }
   }
 }
