@@ -1875,6 +1875,10 @@ void n_tiles_of(bool bf16, bool packed, int rows_max, int bm, int d, int m, int&
 // weights follow the same rule, so that both layouts add in the same order.
 bool use_skinny(int bm, int rows_max, int E) { return bm == kern::SK_BM && 2 * rows_max <= E; }
 
+// every tile holds a row: no more tiles than rows (512 experts, 8 rows: 8
+// instead of 513, whose empty workgroups were most of a small call's time)
+int row_tiles(const Tiles& tl) { return tl.max_tiles < tl.rows_max ? tl.max_tiles : tl.rows_max; }
+
 // kernels are instantiated here, outside any function template (device stubs
 // of kernels first instantiated inside a template launcher are not emitted)
 #define FFN_GEMM(MODE, BM, BN)                                                   \
@@ -1886,6 +1890,7 @@ hipError_t launch_gemm(int mode, int bm, bool wide, const Tiles& tl, const uint1
   if (use_skinny(bm, tl.rows_max, tl.E)) {
     Tiles ts = tl;
     ts.nn = mode == 0 ? m / 32 : d / 64;
+    ts.max_tiles = row_tiles(tl);
     const int grid = (ts.max_tiles * ts.nn + 7) & ~7;
     const RowGather none{nullptr, 1, 0};
     if (mode == 0)
@@ -1966,8 +1971,7 @@ hipError_t launch_packed(int bm, const Tiles& t0, int nn1, const uint16_t* X, co
       // one workgroup per compute unit (two are slower: 2 tokens 42 -> 64 us,
       // 8 tokens 84 -> 89), fewer when the items of at most one tile per row
       // cannot occupy them
-      const int tiles = t0.max_tiles < t0.rows_max ? t0.max_tiles : t0.rows_max;
-      const int most = tiles * (ts.nn > nn1s ? ts.nn : nn1s);
+      const int most = row_tiles(t0) * (ts.nn > nn1s ? ts.nn : nn1s);
       ffn_skinny_kernel<<<grid / 2 < most ? grid / 2 : most, NTHR, 0, s>>>(X, Wgu, Wdn, H, Y, ts, nn1s, d, m, g0,
                                                                           ctr, g);
       return hipGetLastError();
@@ -2002,6 +2006,7 @@ hipError_t launch_packed(int bm, const Tiles& t0, int nn1, const uint16_t* X, co
     if (skinny) {
       Tiles ts = t0;
       ts.nn = m / 32;
+      ts.max_tiles = row_tiles(t0);
       ffn_gemm_skinny_kernel<0, false><<<(ts.max_tiles * ts.nn + 7) & ~7, NTHR, 0, s>>>(A, W, C, ts, d, m, rg, kern::Header{nullptr, 0}, g);
     } else if (bm == 128)
       FFN_PACKED(0, 128);
@@ -2019,6 +2024,7 @@ hipError_t launch_packed(int bm, const Tiles& t0, int nn1, const uint16_t* X, co
     const RowGather rg{nullptr, 1, 0};
     if (skinny) {
       t.nn = d / 64;
+      t.max_tiles = row_tiles(t0);
       ffn_gemm_skinny_kernel<1, false><<<(t.max_tiles * t.nn + 7) & ~7, NTHR, 0, s>>>(A, W, C, t, d, m, rg,
                                                                                       kern::Header{nullptr, 0}, g);
     } else if (bm == 128)

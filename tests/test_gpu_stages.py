@@ -1329,7 +1329,7 @@ def test_persistent_ffn_repeated_calls_bitwise(T, monkeypatch):
 # pair with the k-values split over the wavefronts.  Rows per tile around 32
 # and 64, one to three tiles of an expert, and every remainder of the k loop
 # (k-blocks per wavefront: 4, 8, 12, 16, 24, 32; row-major weights: also 2,
-# 6, 10, 14)
+# 6, 10, 14); many more experts than rows
 @pytest.mark.parametrize("E,d,m,cnt,packed", [
     (16, 2048, 768, [1, 0, 0, 2, 0, 0, 0, 0, 5], True),
     (300, 256, 256, [0, 31, 32, 33, 0, 1], True),
@@ -1340,6 +1340,8 @@ def test_persistent_ffn_repeated_calls_bitwise(T, monkeypatch):
     (150, 768, 384, [3, 0, 66, 1], False),
     (40, 256, 128, [0, 20], False),
     (40, 512, 896, [0, 7, 13], False),
+    (512, 512, 128, [1, 0, 3], False),
+    (1024, 512, 256, [0] * 1020 + [2, 0, 1, 1], True),
 ])
 def test_few_rows_ffn(E, d, m, cnt, packed, monkeypatch):
     counts = np.zeros(E, np.int64)
