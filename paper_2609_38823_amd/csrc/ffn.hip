@@ -1867,13 +1867,24 @@ void n_tiles_of(bool bf16, bool packed, int rows_max, int bm, int d, int m, int&
   }
 }
 
-// Whether the call runs the few-rows items (ffn_skinny_kernel): up to half a
-// row per expert on average, where the wide tiles leave most of the chip idle
-// (Qwen3-VL layer, top-8, clearing launch included: 1 token 61 -> 31 us, 2
-// tokens 65 -> 42, 4 tokens 73 -> 63, 8 tokens 87 -> 84; 23 tokens 108 -> 117,
-// where the wide tiles already stream at the memory's rate).  Row-major
-// weights follow the same rule, so that both layouts add in the same order.
-bool use_skinny(int bm, int rows_max, int E) { return bm == kern::SK_BM && 2 * rows_max <= E; }
+// Whether the call runs the few-rows items (ffn_skinny_kernel): at most half a
+// row per expert on average, and where the wide tiles leave most of the chip
+// idle.  What they save is one wide item's stream, about (d + m - 400) / 200 us;
+// what they cost is a lower streaming rate and more items, about (d m + 176000) /
+// 4.4e6 us for every further expert, of which a row brings at most one.  FFN
+// alone, packed weights, wide tiles -> few-rows items (us), the line in between:
+//   d 2048, m 768, E 128, top-8   1 token 44.4 -> 30.6, 3 56.0 -> 50.3 | 6 63.1 -> 68.0, 8 76.1 -> 80.2
+//   d 2048, m 512, E 256, top-8   4 48.7 -> 42.5                       | 6 54.3 -> 55.5, 16 75.2 -> 94.4
+//   d 1024, m 256, E 512, top-8   4 30.0 -> 27.8                       | 8 32.6 -> 38.3, 32 40.5 -> 61.8
+//   d 512, m 256, E 1024, top-8   3 22.2 -> 21.9                       | 4 22.1 -> 23.1, 64 39.9 -> 66.2
+//   d 512, m 1536, E 64, top-8    3 44.2 -> 39.6, 4 45.1 -> 39.7
+// Row-major weights follow the same rule, so that both layouts add in the same
+// order (d 1024, m 640, E 64, top-6: 3 tokens 26.6 -> 20.2, 4 26.9 -> 28.3; d
+// 2048, m 768, E 128, top-8: 1 35.1 -> 28.1, 3 38.9 -> 46.1).
+bool use_skinny(int bm, int rows_max, int E, int d, int m) {
+  return bm == kern::SK_BM && 2 * rows_max <= E &&
+         (long long)rows_max * ((long long)d * m + 176000) <= 22000ll * (d + m - 400);
+}
 
 // every tile holds a row: no more tiles than rows (512 experts, 8 rows: 8
 // instead of 513, whose empty workgroups were most of a small call's time)
@@ -1887,7 +1898,7 @@ int row_tiles(const Tiles& tl) { return tl.max_tiles < tl.rows_max ? tl.max_tile
 // row-major bf16 weights: one launch per GEMM
 hipError_t launch_gemm(int mode, int bm, bool wide, const Tiles& tl, const uint16_t* A,
                        const uint16_t* W, uint16_t* C, int d, int m, hipStream_t s, const kern::Header hd, Guard g) {
-  if (use_skinny(bm, tl.rows_max, tl.E)) {
+  if (use_skinny(bm, tl.rows_max, tl.E, d, m)) {
     Tiles ts = tl;
     ts.nn = mode == 0 ? m / 32 : d / 64;
     ts.max_tiles = row_tiles(tl);
@@ -1954,7 +1965,7 @@ hipError_t launch_packed(int bm, const Tiles& t0, int nn1, const uint16_t* X, co
                          const uint16_t* Wdn, uint16_t* H, uint16_t* Y, int d, int m,
                          const RowGather g0, int* ctr, hipStream_t s, Guard g, bool counters_ready) {
   int grid = 0, n_xcc = 0;
-  const bool skinny = use_skinny(bm, t0.rows_max, t0.E);
+  const bool skinny = use_skinny(bm, t0.rows_max, t0.E, d, m);
   if (persistent_shape(grid, n_xcc)) {
     if (!counters_ready) {
       hipError_t e = clear_counters(ctr, t0.max_tiles, FFN_PATH_PERSISTENT, s, g);

@@ -1325,11 +1325,12 @@ def test_persistent_ffn_repeated_calls_bitwise(T, monkeypatch):
     assert (s_h[:, 1] == s_h[:, 2]).all() and (s_h[:, 2] == s_h[0, 2]).all() and s_h[0, 2] > 0
 
 
-# at most half a row per expert on average: items of one 32-row weight block
-# pair with the k-values split over the wavefronts.  Rows per tile around 32
-# and 64, one to three tiles of an expert, and every remainder of the k loop
-# (k-blocks per wavefront: 4, 8, 12, 16, 24, 32; row-major weights: also 2,
-# 6, 10, 14); many more experts than rows
+# few rows: items of one 32-row weight block pair with the k-values split over
+# the wavefronts, while rows (d m + 176000) <= 22000 (d + m - 400); the wide
+# tiles beyond.  Rows per tile around 32 and 64, one and two tiles of an
+# expert, and every remainder of the k loop (k-blocks per wavefront: 4, 8, 12,
+# 16, 24, 32, 64; row-major weights: also 2, 6, 10, 14); many more experts
+# than rows
 @pytest.mark.parametrize("E,d,m,cnt,packed", [
     (16, 2048, 768, [1, 0, 0, 2, 0, 0, 0, 0, 5], True),
     (300, 256, 256, [0, 31, 32, 33, 0, 1], True),
@@ -1340,6 +1341,17 @@ def test_persistent_ffn_repeated_calls_bitwise(T, monkeypatch):
     (150, 768, 384, [3, 0, 66, 1], False),
     (40, 256, 128, [0, 20], False),
     (40, 512, 896, [0, 7, 13], False),
+    (140, 4096, 256, [0, 66, 1, 3], True),
+    (120, 2048, 256, [33, 0, 24, 2], True),
+    (24, 256, 256, [0, 9, 1], True),
+    (60, 512, 256, [0, 25, 1], True),
+    (70, 768, 512, [0, 1, 31], True),
+    (72, 1024, 512, [0, 33, 2], True),
+    (200, 2048, 128, [0, 64, 1, 23], False),
+    (240, 4096, 128, [0, 65, 0, 55], False),
+    (70, 512, 384, [0, 28, 1], False),
+    (70, 1024, 640, [32, 0, 1], False),
+    (70, 512, 896, [1, 33], False),
     (512, 512, 128, [1, 0, 3], False),
     (1024, 512, 256, [0] * 1020 + [2, 0, 1, 1], True),
 ])
