@@ -348,9 +348,10 @@ __global__ __launch_bounds__(256) void topk_row_kernel(float* __restrict__ logit
 // bitwise the same slots and weights), else one wavefront per token
 // (topk_select).
 //
-// With `ctr` (a counter that the Top-k launch before this one zeroed), the
-// re-routed entries are also grouped by expert (Algorithm 2's dispatch,
-// x = NULL): every workgroup publishes its entries and counts itself done;
+// With `ctr` (a counter that the Top-k launch before this one zeroed; it may be
+// counts[0], so neither pointer is __restrict__), the re-routed entries are
+// also grouped by expert (Algorithm 2's dispatch, x = NULL): every workgroup
+// publishes its entries and counts itself done;
 // the last one to finish sorts all T k entries (sort_small), so no launch
 // follows for the grouping.  It then also writes the n_zero ints at `zero`
 // (0, and mark_val at index mark_at): the expert FFN's counter header in the
@@ -362,8 +363,8 @@ __global__ __launch_bounds__(CAL_THREADS) void calibrate_route_kernel(
     const float* __restrict__ logits, const int32_t* __restrict__ idx_full,
     const float* __restrict__ w_full, int T, int E, int k, int key_bits, double p,
     double* __restrict__ mass, int32_t* __restrict__ K_out, int32_t* __restrict__ idx,
-    float* __restrict__ w, int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
-    int32_t* __restrict__ src_of_row, int32_t* __restrict__ row_of_slot, int* __restrict__ ctr,
+    float* __restrict__ w, int32_t* counts, int32_t* __restrict__ offsets,
+    int32_t* __restrict__ src_of_row, int32_t* __restrict__ row_of_slot, int* ctr,
     int* __restrict__ zero, int n_zero, int mark_at, int mark_val, const Guard g) {
   static_assert(CAL_THREADS == DS_THREADS && CAL_WAVES == DS_WAVES, "the grouping runs on this workgroup");
   if (guard_skip(g)) return;
@@ -433,7 +434,7 @@ constexpr int ROUTE_SMALL_C = 8;  // logits per lane: E <= 128 (16 per lane spil
 
 template <int RMAXC>  // E <= 16 RMAXC
 __global__ __launch_bounds__(CAL_THREADS) void route_small_kernel(
-    float* __restrict__ logits, const float* __restrict__ part, int S, const float* __restrict__ bias, int T, int E,
+    float* __restrict__ logits, const float* part, int S, const float* __restrict__ bias, int T, int E,
     int k, int key_bits, double p, int32_t* __restrict__ idx_full, float* __restrict__ w_full,
     double* __restrict__ mass, int32_t* __restrict__ K_out, int32_t* __restrict__ idx, float* __restrict__ w,
     int32_t* __restrict__ counts, int32_t* __restrict__ offsets, int32_t* __restrict__ src_of_row,
@@ -487,7 +488,7 @@ __global__ __launch_bounds__(CAL_THREADS) void route_small_kernel(
   const double a = mass_of_entries<1>({ea}, {tid < A ? L.st_w[tid] : 0.f}, 1, E, key_bits,
                                       reinterpret_cast<float*>(L.table) + CAL_WAVES * 16 * ROUTE_SMALL_C, L);
   // the counters that the next launch starts from may lie where the partials
-  // were
+  // were (`part` and `zero` are not __restrict__)
   for (int i = tid; i < n_zero; i += CAL_THREADS) zero[i] = i == mark_at ? mark_val : 0;
   for (int i = tid; i < A; i += CAL_THREADS) {
     idx_full[i] = L.st_e[i];
