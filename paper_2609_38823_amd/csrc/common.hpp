@@ -65,9 +65,9 @@ size_t route_ws_bytes(int T, int d, int E);
 hipError_t launch_route(const void* x, bool x_bf16, const float* w_r, const void* w_r_packed,
                         const float* bias, int T, int d, int E, int k, const int32_t* seg_offsets,
                         int n_seg, const int32_t* K_dev, float* logits, int32_t* idx, float* w,
-                        void* ws, hipStream_t s, Guard g = Guard{}, int* ctr_zero = nullptr);
-// (ctr_zero: an int the Top-k launch sets to 0, for a launch that follows)
-// the Top-k of launch_route on given logits or split partials (part, S)
+                        void* ws, hipStream_t s, Guard g = Guard{});
+// the Top-k of launch_route on given logits or split partials (part, S);
+// ctr_zero: an int the launch sets to 0, for a launch that follows
 hipError_t launch_topk(float* logits, int T, int E, int k, const int32_t* seg_offsets, int n_seg,
                        const int32_t* K_dev, const float* part, int S, const float* bias, int32_t* idx, float* w,
                        hipStream_t s, Guard g = Guard{}, int* ctr_zero = nullptr);

@@ -430,9 +430,8 @@ __global__ __launch_bounds__(CAL_THREADS) void calibrate_route_kernel(
 // selection, same sort).
 // ---------------------------------------------------------------------------
 constexpr int ROUTE_SMALL_T = 16;
-constexpr int ROUTE_SMALL_C = 8;  // logits per lane: E <= 128 (16 per lane spill)
+constexpr int ROUTE_SMALL_C = 8;  // logits per lane: E <= 16 x 8 (16 per lane spill)
 
-template <int RMAXC>  // E <= 16 RMAXC
 __global__ __launch_bounds__(CAL_THREADS) void route_small_kernel(
     float* __restrict__ logits, const float* part, int S, const float* __restrict__ bias, int T, int E,
     int k, int key_bits, double p, int32_t* __restrict__ idx_full, float* __restrict__ w_full,
@@ -444,18 +443,18 @@ __global__ __launch_bounds__(CAL_THREADS) void route_small_kernel(
   const int tid = threadIdx.x, j = tid & 15;
   const int A = T * k;
   const int t = tid >> 4;
-  float v[RMAXC] = {};
+  float v[ROUTE_SMALL_C] = {};
   if (t < T) {
     float* row = logits + (size_t)t * E;
     if (part) {
       // partials in order, then the bias (as topk_kernel); the loads of eight
       // partials in flight together
       for (int sp = 0; sp < S; sp += 8) {
-        float pv[8][RMAXC];
+        float pv[8][ROUTE_SMALL_C];
 #pragma unroll
         for (int u = 0; u < 8; ++u)
 #pragma unroll
-          for (int c = 0; c < RMAXC; ++c) {
+          for (int c = 0; c < ROUTE_SMALL_C; ++c) {
             const int e = j + 16 * c;
             pv[u][c] = sp + u < S && e < E ? part[((size_t)(sp + u) * T + t) * E + e] : 0.f;
           }
@@ -463,11 +462,11 @@ __global__ __launch_bounds__(CAL_THREADS) void route_small_kernel(
         for (int u = 0; u < 8; ++u)
           if (sp + u < S) {
 #pragma unroll
-            for (int c = 0; c < RMAXC; ++c) v[c] = sp + u == 0 ? pv[u][c] : v[c] + pv[u][c];
+            for (int c = 0; c < ROUTE_SMALL_C; ++c) v[c] = sp + u == 0 ? pv[u][c] : v[c] + pv[u][c];
           }
       }
 #pragma unroll
-      for (int c = 0; c < RMAXC; ++c) {
+      for (int c = 0; c < ROUTE_SMALL_C; ++c) {
         const int e = j + 16 * c;
         if (e < E) {
           v[c] += bias ? bias[e] : 0.f;
@@ -476,12 +475,12 @@ __global__ __launch_bounds__(CAL_THREADS) void route_small_kernel(
       }
     } else {
 #pragma unroll
-      for (int c = 0; c < RMAXC; ++c) {
+      for (int c = 0; c < ROUTE_SMALL_C; ++c) {
         const int e = j + 16 * c;
         v[c] = e < E ? row[e] : 0.f;
       }
     }
-    row_topk_select<RMAXC>(v, j, E, k, E, L.st_e + t * k, L.st_w + t * k);
+    row_topk_select<ROUTE_SMALL_C>(v, j, E, k, E, L.st_e + t * k, L.st_w + t * k);
   }
   __syncthreads();  // the entries are in LDS; every partial has been read
   const int ea = tid < A ? L.st_e[tid] : -1;
@@ -498,7 +497,7 @@ __global__ __launch_bounds__(CAL_THREADS) void route_small_kernel(
   if (tid < E) mass[tid] = a;
   if (tid == 0) K_out[0] = K;
   const int Klim = clampi(K, k, E);
-  if (t < T) row_topk_select<RMAXC>(v, j, E, k, Klim, L.st_e + t * k, L.st_w + t * k);
+  if (t < T) row_topk_select<ROUTE_SMALL_C>(v, j, E, k, Klim, L.st_e + t * k, L.st_w + t * k);
   __syncthreads();
   for (int i = tid; i < A; i += CAL_THREADS) {
     idx[i] = L.st_e[i];
@@ -512,7 +511,13 @@ __global__ __launch_bounds__(CAL_THREADS) void route_small_kernel(
 
 // One launch up to CAL_SORT_A entries, the grouping's sort by its last
 // workgroup included (12 248 entries, E 128: 36 us, where masses, re-route,
-// histogram, ranks and the FFN's clearing launch took 68).
+// histogram, ranks and the FFN's clearing launch took 68).  Every workgroup of
+// 16 tokens forms the masses of all, and one fits a compute unit: with few
+// entries per token that is several rounds over the chip, and still ahead of
+// the one workgroup per segment of the two launches, which is bound by its
+// chain of tokens (calibration and re-route, two launches -> one: E 64, k 1,
+// 10000 tokens 221 -> 119 us, 16384 355 -> 243; E 512, k 1, 16384 743 -> 245;
+// E 64, k 2, 8192 184 -> 111).
 bool calibrate_route_fused(int T, int E, int k) {
   return T >= 1 && cal_sorted((size_t)T * k, E, k);
 }
@@ -560,7 +565,7 @@ hipError_t launch_topk_calibrate_sort(float* logits, const float* part, int S, c
   if (route_small(T, E, k)) {
     int key_bits = 0;
     while ((1 << key_bits) < E) ++key_bits;
-    route_small_kernel<ROUTE_SMALL_C><<<1, CAL_THREADS, 0, s>>>(
+    route_small_kernel<<<1, CAL_THREADS, 0, s>>>(
         logits, part, S, bias, T, E, k, key_bits, p, idx_full, w_full, mass, K_out, idx, w, so.counts, so.offsets,
         so.src_of_row, so.row_of_slot, so.zero, so.n_zero, so.mark_at, so.mark_val, g);
     return hipGetLastError();
@@ -570,15 +575,17 @@ hipError_t launch_topk_calibrate_sort(float* logits, const float* part, int S, c
   return launch_calibrate_route(logits, idx_full, w_full, T, E, k, p, mass, K_out, idx, w, s, g, &so);
 }
 
-bool route_rcep_fused(int T, int E, int k) {
-  return calibrate_route_fused(T, E, k) && (size_t)T * k <= (size_t)DS_MAX && E <= DS_THREADS;
-}
+// cal_sorted() bounds the entries by CAL_SORT_A = DS_MAX and E by CAL_SORT_E <=
+// DS_THREADS, which is what the grouping's sort holds
+bool route_rcep_fused(int T, int E, int k) { return calibrate_route_fused(T, E, k); }
+static_assert(CAL_SORT_A <= DS_MAX && CAL_SORT_E <= DS_THREADS, "the grouping's sort holds what the masses do");
 
 size_t route_rcep_ws_bytes(int T, int d, int E, int k) {
   const size_t a = route_x3_ws_bytes(T, d, E);
-  // up to 8192 entries nothing but the partials is written; the 256 bytes
-  // more are part of the call's contract, and so is the dispatch's part above
-  if (T >= 1 && (size_t)T * k <= 8192 && E <= CAL_SORT_E) return (a + 255) / 256 * 256 + 256;
+  // up to CAL_STAGE entries nothing but the partials is written; the 256 bytes
+  // more are part of the call's contract (a workspace without them is refused),
+  // and so is the dispatch's part above, also where one launch needs none
+  if (T >= 1 && (size_t)T * k <= (size_t)CAL_STAGE && E <= CAL_SORT_E) return (a + 255) / 256 * 256 + 256;
   const size_t b = dispatch_ws_bytes(T, k, E);
   return a > b ? a : b;
 }
@@ -655,7 +662,7 @@ size_t route_ws_bytes(int T, int d, int E) {
 hipError_t launch_route(const void* x, bool x_bf16, const float* w_r, const void* w_r_packed,
                         const float* bias, int T, int d, int E, int k, const int32_t* seg_offsets,
                         int n_seg, const int32_t* K_dev, float* logits, int32_t* idx, float* w,
-                        void* ws, hipStream_t s, Guard g, int* ctr_zero) {
+                        void* ws, hipStream_t s, Guard g) {
   float* part = nullptr;
   int S = 1;
   if (x && w_r_packed) {
@@ -680,7 +687,7 @@ hipError_t launch_route(const void* x, bool x_bf16, const float* w_r, const void
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
   }
-  return launch_topk(logits, T, E, k, seg_offsets, n_seg, K_dev, part, S, bias, idx, w, s, g, ctr_zero);
+  return launch_topk(logits, T, E, k, seg_offsets, n_seg, K_dev, part, S, bias, idx, w, s, g);
 }
 
 hipError_t launch_topk(float* logits, int T, int E, int k, const int32_t* seg_offsets, int n_seg,
