@@ -417,12 +417,14 @@ def test_calibrate_prefix_exact(T, E, k, segs, p):
     np.testing.assert_array_equal(host(order), ro)
 
 
-@pytest.mark.parametrize("T,E,k", [(300, 16, 2), (1500, 128, 8)])
+@pytest.mark.parametrize("T,E,k", [(300, 16, 2), (1500, 128, 8), (2049, 128, 8), (409, 40, 20), (410, 40, 20),
+                                   (60, 600, 8)])
 def test_calibrate_skips_out_of_range_entries(T, E, k):
     """Routing entries with an expert outside [0, E) add nothing to the
     masses: the result is bitwise that of the same routing with those
-    entries' weights set to zero (sorted path, and the chunked path above
-    8192 entries)."""
+    entries' weights set to zero (the sorted masses: up to 2048 tokens at
+    k = 8, up to 8192 entries at k = 20; the chunked ones beyond, and above
+    512 experts)."""
     idx, w = I.synthetic_routing(T, E, k, seed=T + 5)
     rng = np.random.default_rng(T)
     bad = rng.choice(idx.size, size=idx.size // 53, replace=False)
@@ -541,7 +543,13 @@ def test_calibrate_worked_example_golden():
     (200, 256, 8, 0.9),    # 128 < E <= 256: rows of 16 lanes, 16 values per lane
     (150, 200, 20, 0.8),   # k > 16: one wavefront per token
     (300, 512, 16, 0.95),  # E = 512, the largest one-launch pool
-    (2000, 64, 8, 0.9),    # 16000 entries: the two-launch path
+    (2000, 64, 8, 0.9),    # one launch (16000 entries)
+    (2048, 128, 8, 0.9),   # one launch at the 16384-entry limit
+    (2049, 128, 8, 0.9),   # the two-launch path
+    (4096, 64, 4, 0.9),    # one launch at the limit, k = 4
+    (4097, 64, 4, 0.9),    # the two-launch path
+    (410, 256, 20, 0.9),   # k > 16 and E <= 256 above 8192 entries: the two-launch path
+    (410, 300, 20, 0.9),   # k > 16, E > 256: one launch (8200 entries)
     (100, 600, 4, 0.9),    # E > 512: the two-launch path
 ])
 def test_calibrate_route_prefix_matches_two_calls(T, E, k, p):
@@ -573,10 +581,10 @@ def test_calibrate_route_prefix_matches_two_calls(T, E, k, p):
 # moe_route_rcep: router, full-pool Top-k, masses, K, prefix re-route and
 # grouping of one invocation in one call, bitwise the separate calls
 # ---------------------------------------------------------------------------
-# up to 8192 entries: the router and Top-k, then calibration, re-route and
-# the grouping in one launch (the last workgroup to finish sorts; one
-# workgroup at 1 row, four at 63 and 64, five at 65, 64 at 1024); beyond:
-# the separate launches
+# up to 16384 entries at k = 8: the router and Top-k, then calibration,
+# re-route and the grouping in one launch (the last workgroup to finish sorts;
+# four workgroups at 63 and 64 rows, five at 65, 65 at 1025; at 1 row one
+# workgroup does the Top-k too); beyond (4096): the separate launches
 @pytest.mark.parametrize("shape,T", [("qwen", 512), ("qwen", 64), ("qwen", 1), ("qwen", 63), ("qwen", 65),
                                      ("qwen", 1024), ("qwen", 1025), ("qwen", 4096), ("e96", 333), ("d64", 50),
                                      ("e256", 300), ("e256", 40), ("e256k20", 100), ("e256k20", 500),
@@ -722,14 +730,17 @@ ALL_OUTS = ("logits", "idx_full", "w_full", "mass", "K", "idx", "w", "counts", "
             "out")
 
 
-# T*k <= 8192: the routing's one-launch grouping also clears the expert
-# FFN's counters (qwen 1, 64, 512, 1024; e64; e256k20); beyond, the
-# separate launches with the FFN's own clearing (qwen 1025, e64 2100)
+# the routing's one-launch grouping also clears the expert FFN's counters (up
+# to qwen 2048, e64 4096, e256k20 409); beyond, the separate launches with the
+# FFN's own clearing (qwen 2049, e64 4097, e256k20 410)
 # (no_res: residual NULL, the plain combine)
 @pytest.mark.parametrize("shape,T,no_res", [("qwen", 512, False), ("qwen", 64, False), ("qwen", 1, False),
                                             ("qwen", 1024, False), ("qwen", 1025, False), ("e64", 300, False),
                                             ("e64", 2100, False), ("e256k20", 100, False), ("e64", 0, False),
-                                            ("qwen", 512, True), ("qwen", 1025, True), ("e64", 300, True)])
+                                            ("qwen", 512, True), ("qwen", 1025, True), ("e64", 300, True),
+                                            ("qwen", 2048, False), ("qwen", 2049, False), ("qwen", 2049, True),
+                                            ("e64", 4096, True), ("e64", 4097, False), ("e256k20", 409, False),
+                                            ("e256k20", 410, False)])
 def test_rcep_layer_matches_separate_calls(shape, T, no_res):
     sh = RCEP_LAYER_SHAPES[shape]
     L = _RcepLayer(sh, seed=13)
@@ -813,10 +824,11 @@ def test_dense_layer_matches_separate_calls(shape, T, no_res):
     _assert_same(a, b, DENSE_OUTS)
 
 
-# qwen 1, 64, 512, e64: the previous combine inside the router's launch;
-# qwen 1025 (T*k > 8192) and e256k20 (E > 128): the combine on its own first
+# up to qwen 2048 and e64 4096: the previous combine inside the router's
+# launch; qwen 2049, e64 4097 (the separate routing launches) and e256k20
+# (E > 128): the combine on its own first
 @pytest.mark.parametrize("shape,T", [("qwen", 64), ("qwen", 512), ("qwen", 1), ("qwen", 1025), ("e64", 300),
-                                     ("e256k20", 100)])
+                                     ("e256k20", 100), ("qwen", 2048), ("qwen", 2049), ("e64", 4097)])
 @pytest.mark.parametrize("shared", [False, True])
 def test_rcep_layer_chained_matches_separate_calls(shape, T, shared):
     """Two layers through moe_rcep_layer_chained (the first without a
@@ -850,7 +862,8 @@ def test_rcep_layer_chained_matches_separate_calls(shape, T, shared):
     _assert_same(a1, b1, ALL_OUTS[:-1])
 
 
-@pytest.mark.parametrize("shape,T", [("qwen", 64), ("qwen", 1025), ("e64", 300)])
+# (qwen 1025: the separate routing launches at 2050 rows, then one launch)
+@pytest.mark.parametrize("shape,T", [("qwen", 64), ("qwen", 1025), ("e64", 300), ("e64", 4097)])
 def test_rcep_layer_in_place_and_reused_workspace(shape, T):
     """out == residual == x (the hidden state updated in place), on one
     workspace reused by a larger then a smaller call: bitwise the separate
