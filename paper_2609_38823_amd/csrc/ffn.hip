@@ -1878,12 +1878,17 @@ void n_tiles_of(bool bf16, bool packed, int rows_max, int bm, int d, int m, int&
 //   d 1024, m 256, E 512, top-8   4 30.0 -> 27.8                       | 8 32.6 -> 38.3, 32 40.5 -> 61.8
 //   d 512, m 256, E 1024, top-8   3 22.2 -> 21.9                       | 4 22.1 -> 23.1, 64 39.9 -> 66.2
 //   d 512, m 1536, E 64, top-8    3 44.2 -> 39.6, 4 45.1 -> 39.7
-// Row-major weights follow the same rule, so that both layouts add in the same
-// order (d 1024, m 640, E 64, top-6: 3 tokens 26.6 -> 20.2, 4 26.9 -> 28.3; d
-// 2048, m 768, E 128, top-8: 1 35.1 -> 28.1, 3 38.9 -> 46.1).
+// Row-major weights follow the same rule where they could be packed, so that both
+// layouts add in the same order (d 2048, m 768, E 128, top-8: 1 token 35.1 -> 28.1,
+// 3 38.9 -> 46.1; clearing and wide tiles of one workgroup per compute unit took
+// 61 and 81).  Widths that only they take (m not a multiple of 256) stream more
+// slowly in 32-row blocks, 7/5 of the weights' share: d 1280, m 896, E 64, top-6:
+// 3 tokens 35 -> 35.9, 4 35 -> 44.6; d 2048, m 640, E 384, top-8: 2 40.1 -> 38.0, 4
+// 42.7 -> 47.0; d 1024, m 640, E 64, top-6: 3 26.6 -> 20.2, 4 26.9 -> 28.3.
 bool use_skinny(int bm, int rows_max, int E, int d, int m) {
-  return bm == kern::SK_BM && 2 * rows_max <= E &&
-         (long long)rows_max * ((long long)d * m + 176000) <= 22000ll * (d + m - 400);
+  const long long dm = (long long)d * m;
+  const long long per_row = (m % 256 == 0 ? dm : dm * 7 / 5) + 176000;
+  return bm == kern::SK_BM && 2 * rows_max <= E && rows_max * per_row <= 22000ll * (d + m - 400);
 }
 
 // every tile holds a row: no more tiles than rows (512 experts, 8 rows: 8

@@ -1339,8 +1339,8 @@ def test_persistent_ffn_repeated_calls_bitwise(T, monkeypatch):
 
 
 # few rows: items of one 32-row weight block pair with the k-values split over
-# the wavefronts, while rows (d m + 176000) <= 22000 (d + m - 400); the wide
-# tiles beyond.  Rows per tile around 32 and 64, one and two tiles of an
+# the wavefronts, while rows (d m + 176000) <= 22000 (d + m - 400) (7/5 d m where
+# m is not a multiple of 256); the wide tiles beyond.  Rows per tile around 32 and 64, one and two tiles of an
 # expert, and every remainder of the k loop (k-blocks per wavefront: 4, 8, 12,
 # 16, 24, 32, 64; row-major weights: also 2, 6, 10, 14); many more experts
 # than rows
@@ -1360,11 +1360,12 @@ def test_persistent_ffn_repeated_calls_bitwise(T, monkeypatch):
     (60, 512, 256, [0, 25, 1], True),
     (70, 768, 512, [0, 1, 31], True),
     (72, 1024, 512, [0, 33, 2], True),
-    (200, 2048, 128, [0, 64, 1, 23], False),
-    (240, 4096, 128, [0, 65, 0, 55], False),
-    (70, 512, 384, [0, 28, 1], False),
-    (70, 1024, 640, [32, 0, 1], False),
-    (70, 512, 896, [1, 33], False),
+    (200, 2048, 128, [0, 64, 1, 5], False),
+    (240, 4096, 128, [0, 65, 0, 27], False),
+    (80, 2048, 384, [0, 34, 1], False),
+    (70, 512, 384, [0, 23, 1], False),
+    (70, 1024, 640, [24, 0, 1], False),
+    (70, 512, 896, [1, 26], False),
     (512, 512, 128, [1, 0, 3], False),
     (1024, 512, 256, [0] * 1020 + [2, 0, 1, 1], True),
 ])
