@@ -1847,10 +1847,11 @@ int pick_bm(int rows_max, int E, bool packed) { return rows_max >= (packed ? 48 
 // n-tiles per GEMM.  Row-major bf16 weights: 256-row weight tiles, and 512 at
 // 128-row token tiles where 512 divides the expert's rows (gate/up: 2m, down:
 // d) and half the compute units get a whole tile each (64-row token tiles run
-// two workgroups per compute unit at 256: both GEMMs of d 1024, m 640, 64
-// experts, top-6, 128 tokens 54.3 -> 46.5 us, 1200 tokens 102 -> 92, 777
-// tokens 70.2 -> 71.7; d 512, m 384, 48 experts, top-4, 2048 tokens, 128-row
-// token tiles 35.3 -> 28.4).  The packed kernel's two-launch form always
+// two workgroups per compute unit at 256, 512 one: the whole call, evenly routed,
+// with the clearing launch that went with it: d 1024, m 640, 64 experts, top-6, 128
+// tokens 60.0 -> 49.9 us, 777 84.2 -> 75.1, 1200 100.7 -> 85.8; d 4096, m 1408,
+// 16 experts, top-2, 128 tokens 143.6 -> 128.1; d 512, m 384, 48 experts, top-4,
+// 2048 tokens, 128-row token tiles 46.5 -> 38.8).  The packed kernel's two-launch form always
 // takes 256.  float32: 32 columns of h, 64 output columns.
 void n_tiles_of(bool bf16, bool packed, int rows_max, int bm, int d, int m, int& nn0, int& nn1, bool& wide0,
                 bool& wide1) {
