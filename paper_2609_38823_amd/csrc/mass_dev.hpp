@@ -40,6 +40,7 @@ constexpr int CAL_SORT_E = 512;  // the sorted path keeps [waves][E] counts in t
 // where few tokens make many entries (calibration + re-route of 262 tokens, k 32:
 // E 32 24.7 us against 26.6, E 256 31.5 against 34.1, E 512 51.9 against 43.9;
 // 525 tokens, k 16: E 32 25.3 against 24.1, E 256 32.6 against 32.3).
+// (Rounds for all CAL_SORT_A entries where k does not divide 64, up to 24, spill.)
 __host__ __device__ inline bool cal_sorted(size_t n_all, int E, int k) {
   if (E > CAL_SORT_E) return false;
   if (n_all <= (size_t)CAL_STAGE) return true;
@@ -138,10 +139,10 @@ __device__ double mass_chunked(const int32_t* __restrict__ idx, const float* __r
 
 // The same from this thread's entries (key, weight) in the slices of
 // sort_dev.hpp; `sorted` (LDS) holds the weights grouped by expert.
-// token_mask: the earlier lanes of this lane's token, where rounds hold whole
-// tokens and repeated experts are looked for (L.repeats is then set if a token
+// REPEATS: rounds hold whole tokens and repeated experts are looked for, token_mask
+// being the earlier lanes of this lane's token (L.repeats is then set if a token
 // names an expert twice, and the masses are not what is wanted).
-template <int R>
+template <int R, bool REPEATS = false>
 __device__ __forceinline__ double mass_of_entries(const int (&key)[R], const float (&rw)[R], int nr, int E,
                                                   int key_bits, float* sorted, CalLds& L, uint64_t token_mask = 0) {
   const int tid = threadIdx.x, wv = tid >> 6;
@@ -151,9 +152,9 @@ __device__ __forceinline__ double mass_of_entries(const int (&key)[R], const flo
   slice_scan<R>(key, nr, E, wh, E, L.part, cnt, first);
   rank_rounds<R>(key, nr, E, key_bits, wh + wv * E, [&](int r, int pos, int, uint64_t peers) {
     if (pos >= 0) sorted[pos] = rw[r];
-    again |= pos >= 0 ? peers & token_mask : 0;
+    if constexpr (REPEATS) again |= pos >= 0 ? peers & token_mask : 0;
   });
-  if (again) L.repeats = 1;
+  if (REPEATS && again) L.repeats = 1;
   __syncthreads();
   double a = 0.0;
   if (tid < E) {
@@ -177,7 +178,7 @@ __device__ __forceinline__ double mass_sorted(const int32_t* __restrict__ idx, c
   const int lane = threadIdx.x & 63;
   const size_t base = (size_t)lo_t * k;
   double mass = 0.0;
-  auto run = [&](auto RC, int W, int nr, uint64_t token_mask) {
+  auto run = [&](auto RC, auto REP, int W, int nr, uint64_t token_mask) {
     constexpr int R = decltype(RC)::value;
     const int lo = slice_lo(n_all, nr, W), hi = lane < W ? min(n_all, lo + nr * W) : 0;
     int key[R];
@@ -189,17 +190,18 @@ __device__ __forceinline__ double mass_sorted(const int32_t* __restrict__ idx, c
       key[r] = in ? idx[base + a] : -1;
       rw[r] = in ? w[base + a] : 0.f;
     }
-    mass = mass_of_entries<R>(key, rw, nr, E, key_bits, reinterpret_cast<float*>(L.st_e), L, token_mask);
+    mass = mass_of_entries<R, decltype(REP)::value>(key, rw, nr, E, key_bits, reinterpret_cast<float*>(L.st_e), L,
+                                                    token_mask);
   };
   if (n_all <= CAL_STAGE) {
     const int nr = slice_rounds(n_all);
-    with_rounds<DS_R / 2>(nr, [&](auto RC) { run(RC, kWave, nr, 0); });
+    with_rounds<DS_R / 2>(nr, [&](auto RC) { run(RC, std::false_type{}, kWave, nr, 0); });
   } else {
     // beyond CAL_STAGE entries: rounds of whole tokens (64 entries where k
     // divides 64), so that a token's repeated experts meet in one round
     if (threadIdx.x == 0) L.repeats = 0;  // (slice_scan's barriers order it before the ranks)
     const int W = kWave / k * k;
-    run(std::integral_constant<int, DS_R>{}, W, slice_rounds(n_all, W),
+    run(std::integral_constant<int, DS_R>{}, std::true_type{}, W, slice_rounds(n_all, W),
         ((1ull << lane) - 1) & ~((1ull << (lane - lane % k)) - 1));
     if (L.repeats) mass = mass_chunked(idx, w, lo_t, lo_t + n_all / k, E, k, L);
   }

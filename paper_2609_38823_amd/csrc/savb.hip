@@ -70,8 +70,9 @@ __device__ __forceinline__ float last_row(const void* rows, int n, int d, int c)
               : static_cast<const float*>(rows)[(size_t)(n - 1) * d + c];
 }
 
-// PRE: 16-byte weight loads per lane that are in flight ahead of a unit
-template <bool BF16, int PRE>
+// PRE: 16-byte weight loads per lane that are in flight ahead of a unit; MULTI:
+// several units per wavefront
+template <bool BF16, int PRE, bool MULTI>
 __global__ __launch_bounds__(256) void savb_mlp_kernel(
     const void* __restrict__ rows, int n, int d, int splits, const float* __restrict__ partial,
     float* __restrict__ feature, const float* __restrict__ w1, const float* __restrict__ b1, int hid,
@@ -133,14 +134,9 @@ __global__ __launch_bounds__(256) void savb_mlp_kernel(
   __syncthreads();
   if (feature && blockIdx.x == 0)
     for (int c = tid; c < 2 * d; c += 256) feature[c] = xs[c];
-  for (int u = blockIdx.x * 4 + wv; u < hid; u += gridDim.x * 4) {
+  auto unit = [&](int u, const float4 (&c)[PRE], float b) {
     const float* wr = w1 + (size_t)u * 2 * d;
     float acc = 0.f;
-    const float b = bu;
-    float4 c[PRE];
-#pragma unroll
-    for (int q = 0; q < PRE; ++q) c[q] = v[q];
-    if (u + (int)gridDim.x * 4 < hid) first_weights(u + gridDim.x * 4);
     auto add4 = [&](const float4& w, int j) {
       const float4 x = *reinterpret_cast<const float4*>(xs + 4 * j);
       acc = fmaf(w.x, x.x, acc);
@@ -177,6 +173,19 @@ __global__ __launch_bounds__(256) void savb_mlp_kernel(
     if (lane == 0)
       __hip_atomic_store(hidden + u, fmaxf(acc + b, 0.f), __ATOMIC_RELAXED,
                          __HIP_MEMORY_SCOPE_AGENT);
+  };
+  int u = blockIdx.x * 4 + wv;
+  if constexpr (MULTI) {
+    for (; u < hid; u += gridDim.x * 4) {
+      const float b = bu;
+      float4 c[PRE];
+#pragma unroll
+      for (int q = 0; q < PRE; ++q) c[q] = v[q];
+      if (u + (int)gridDim.x * 4 < hid) first_weights(u + gridDim.x * 4);
+      unit(u, c, b);
+    }
+  } else if (u < hid) {
+    unit(u, v, bu);
   }
   // every unit of the workgroup is stored (vmcnt 0), then it counts itself;
   // the last one decides
@@ -190,17 +199,18 @@ __global__ __launch_bounds__(256) void savb_mlp_kernel(
   float* z = xs;
   if (wv < 2) {  // class = wavefront
     float acc = 0.f;
-    for (int h0 = lane; h0 < hid; h0 += 64 * 8) {  // eight loads in flight, added in order
+    for (int h0 = 0; h0 < hid; h0 += 64 * 8) {  // eight loads in flight, added in order
       float hv[8], wq[8];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const int h = min(h0 + 64 * q, hid - 1);
-        hv[q] = __hip_atomic_load(hidden + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        wq[q] = w2[(size_t)wv * hid + h];
-      }
+      for (int q = 0; q < 8; ++q)
+        if (h0 + 64 * q < hid) {  // (the same for all lanes)
+          const int h = min(h0 + 64 * q + lane, hid - 1);
+          hv[q] = __hip_atomic_load(hidden + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          wq[q] = w2[(size_t)wv * hid + h];
+        }
 #pragma unroll
       for (int q = 0; q < 8; ++q)
-        if (h0 + 64 * q < hid) acc = fmaf(wq[q], hv[q], acc);
+        if (h0 + 64 * q + lane < hid) acc = fmaf(wq[q], hv[q], acc);
     }
     for (int off = 32; off >= 1; off >>= 1) acc += __shfl_down(acc, off, 64);
     if (lane == 0) z[wv] = acc + bz;
@@ -266,13 +276,16 @@ hipError_t launch_savb_gate(const void* rows, bool bf16, int n, int d, const flo
   if (e != hipSuccess) return e;
   const unsigned hb = std::min(SG_WGS, (unsigned)((hid + 3) / 4));
   const size_t lds = (size_t)2 * d * sizeof(float);
-#define SAVB_MLP(BF16, PRE)                                                                                      \
-  savb_mlp_kernel<BF16, PRE><<<hb, 256, lds, s>>>(rows, n, d, splits, partial, feature, w1, b1, hid, hidden, w2, b2, \
-                                                  theta, p_exit, exit_flag, exit_layer, layer, ctr, g)
-  if (d <= 512) {
-    if (bf16) SAVB_MLP(true, 4); else SAVB_MLP(false, 4);
+  const bool multi = hid > 4 * (int)hb;
+#define SAVB_MLP(BF16, PRE, MULTI)                                                                                  \
+  savb_mlp_kernel<BF16, PRE, MULTI><<<hb, 256, lds, s>>>(rows, n, d, splits, partial, feature, w1, b1, hid, hidden, \
+                                                         w2, b2, theta, p_exit, exit_flag, exit_layer, layer, ctr, g)
+  if (multi) {
+    if (bf16) SAVB_MLP(true, 16, true); else SAVB_MLP(false, 16, true);
+  } else if (d <= 512) {
+    if (bf16) SAVB_MLP(true, 4, false); else SAVB_MLP(false, 4, false);
   } else {
-    if (bf16) SAVB_MLP(true, 16); else SAVB_MLP(false, 16);
+    if (bf16) SAVB_MLP(true, 16, false); else SAVB_MLP(false, 16, false);
   }
 #undef SAVB_MLP
   return hipGetLastError();
