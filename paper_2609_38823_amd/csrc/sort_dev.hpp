@@ -31,8 +31,9 @@ __device__ __forceinline__ int slice_lo(int A, int nr, int W = kWave) {
 // `run` (this wavefront's next position per expert, in LDS) advances from
 // round to round.  The ballots of up to four rounds are formed together, ahead
 // of the chain through `run` (8192 entries: the whole sort 10.3 -> 8.6 us);
-// the last rounds are not filled up to four (2048 entries, two rounds, the whole
-// sort with 1024 experts: 7.3 -> 6.4 us).
+// a last one or two rounds are not filled up to four (2048 entries, two rounds, the
+// whole sort with 1024 experts: 7.3 -> 6.4 us; forms for one and for three rounds
+// too grow the code and were 1-4 % slower in the calibration).
 // emit(round, position, key, lanes of this round with the same key) is called
 // with position -1 for keys outside [0, E).
 template <int R0, int Q, int R, class Emit>
@@ -73,12 +74,8 @@ __device__ __forceinline__ void rank_rounds(const int (&key)[R], int nr, int E, 
       rank_group<R0, 1>(key, E, key_bits, run, emit);
       rank_rounds<R, R0 + 1>(key, nr, E, key_bits, run, emit);
     } else {
-      if (left == 1)
-        rank_group<R0, 1>(key, E, key_bits, run, emit);
-      else if (left == 2)
+      if (left <= 2)
         rank_group<R0, 2>(key, E, key_bits, run, emit);
-      else if (left == 3)
-        rank_group<R0, 3>(key, E, key_bits, run, emit);
       else
         rank_group<R0, 4>(key, E, key_bits, run, emit);
       rank_rounds<R, R0 + 4>(key, nr, E, key_bits, run, emit);
